@@ -444,15 +444,53 @@ int cell_bucket(float u) {
   return (int)fminf(fmaxf(floorf(u * h), -h), h - 1.0f) + quasar::kCellBuckets / 2;
 }
 
+// Cells per lane of the binned kernel for n_cells cells.
+int int_cells_per_lane(int n_cells, int group, bool split) {
+  const int L = group / 16;
+  return quasar::int_cells_round(split, (n_cells + L - 1) / L);
+}
+
+// Whether the binned INT kernel serves a grid of n_cells cells, and in which
+// form.  Up to 10 cells a lane it holds both sums in a cell and is the faster
+// kernel for any number of clips.  With more cells it takes one sum at a time
+// (split), and the direct kernel's time grows with the clips instead: on the
+// Llama-3.1-8B layer set, INT3 g128 with 15 clips, split 727 us against 1172
+// direct (two passes over the weights); INT3 g64 with 10 clips 768 against
+// 987 (a pass of 12 at three wavefronts per SIMD); with 8 clips (INT4 g128,
+// one pass at four) 760 against 745.
+bool int_cells_fit(int n_cells, int K, int group, bool any_fit, bool& split) {
+  if (n_cells > 128 || n_cells + 2 > quasar::kCellThr) return false;
+  split = int_cells_per_lane(n_cells, group, false) > quasar::int_cells_most(false);
+  if (!split) return true;
+  if (!any_fit && K <= 8) return false;
+  return int_cells_per_lane(n_cells, group, true) <= quasar::int_cells_most(true);
+}
+
+// The 512-bucket table for the sorted thresholds s[0 .. m): base[b] = the
+// number of thresholds below bucket b or at its least u.  False when a bucket
+// holds more than one other threshold.
+bool int_one_compare(uint8_t* base, const float* s, int m, float shift) {
+  auto bucket = [&](float u) {
+    return (int)fminf(fmaxf(floorf(fmaf(u, 256.0f, shift)), -256.0f), 255.0f) + 256;
+  };
+  int i = 0;
+  for (int b = 0; b < quasar::kIntBuckets; b++) {
+    while (i < m && bucket(s[i]) == b && bucket(nextafterf(s[i], -INFINITY)) < b) i++;
+    base[b] = (uint8_t)i;
+    int inside = 0;
+    for (; i < m && bucket(s[i]) == b; i++) inside++;
+    if (inside > 1) return false;
+  }
+  return true;
+}
+
 // The binned INT kernel's tables for this clip grid (int_cells_kernel.hip):
 // every threshold T(k, b) = the least fp32 u with code_k(u) >= q0 + b, found
 // by bisection over the ordered fp32 values between -inf (the lowest code)
 // and +inf (the highest).  Leaves n_cells = 0 -- the direct kernel runs --
-// when the cells do not fit the kernel's LDS budget, when a lane would scan
-// more than kCellsPerLaneAuto cells (the binned kernel's per-cell LDS work
-// then outweighs the per-clip work it saves: INT4 grids), when a bucket
-// needs more than three compares, or when QUASAR_INT_PATH=direct is set.
-// QUASAR_INT_PATH=binned takes the binned kernel wherever its tables fit.
+// when int_cells_fit says so, when a bucket needs more than three compares, or
+// when QUASAR_INT_PATH=direct is set.  QUASAR_INT_PATH=binned takes the binned
+// kernel wherever its tables fit.
 //
 // With odd qmax every clip has a threshold just below u = 0, where the fp32
 // code rounding ties at qmax/2: T(k, (qmax+1)/2) lies in (-2^-20, 0).  These
@@ -466,18 +504,14 @@ void int_cells(quasar::IntParams& p, int K, int bits, bool sym, int group) {
   const char* force = getenv("QUASAR_INT_PATH");
   if (force != nullptr && strcmp(force, "direct") == 0) return;
   const bool any_fit = force != nullptr && strcmp(force, "binned") == 0;
+  bool split = false;
   const int qmax = sym ? (1 << (bits - 1)) - 1 : (1 << bits) - 1;
   const int q0 = sym ? -qmax : 0;
   const int nb = sym ? 2 * qmax : qmax;
   const int tie = sym ? 0 : (qmax + 1) / 2;  // step b whose thresholds are the tie cluster
-  const int L = group / 16;
-  {
-    // at most K nb thresholds (the tie ones count once): when even that many
-    // fit, or when they cannot fit at all, this is decided before any search
-    const int m_upper = K * nb - (tie > 0 ? K - 2 : 0);
-    const int limit = any_fit ? quasar::kCellsPerLane : quasar::kCellsPerLaneAuto;
-    if ((m_upper + 1 + L - 1) / L > limit) return;
-  }
+  // at most K nb thresholds (the tie ones count once): when that many do not
+  // fit, this is decided before any search
+  if (!int_cells_fit(K * nb - (tie > 0 ? K - 2 : 0) + 1, K, group, any_fit, split)) return;
   float t[quasar::kMaxClips * quasar::kCellSteps];
   int n = 0;
   float ulo = INFINITY, uhi = -INFINITY;
@@ -524,18 +558,26 @@ void int_cells(quasar::IntParams& p, int K, int bits, bool sym, int group) {
     for (int i = 0; i < m; i++)
       if (srt[i] > ulo && srt[i] <= uhi) return;
   }
-  const int cpl = (m + 1 + L - 1) / L;
-  if (cpl > quasar::kCellsPerLane || m + 3 > quasar::kCellThr || m > 127) return;
-  if (!any_fit && cpl > quasar::kCellsPerLaneAuto) return;
-  int cnt[quasar::kCellBuckets] = {0};
-  int cmax = 1, below = 0;
-  for (int i = 0; i < m; i++) cnt[cell_bucket(srt[i])]++;
-  for (int b = 0; b < quasar::kCellBuckets; b++) {
-    cmax = std::max(cmax, cnt[b]);
-    p.cells.base[b] = (uint8_t)below;
-    below += cnt[b];
+  if (!int_cells_fit(m + 1, K, group, any_fit, split)) return;
+  const int cpl = int_cells_per_lane(m + 1, group, split);
+  // One compare per weight when 512 buckets leave at most one threshold
+  // inside each: a bucket edge is put exactly on the unsafe cell's upper end
+  // (the lower end lies less than 2^-20 below it), and a threshold that is
+  // the least u of its bucket needs no compare.
+  const float shift = merge ? -256.0f * nextafterf(uhi, INFINITY) : 0.0f;
+  int cmax = int_one_compare(p.cells.base, srt, m, shift) ? 1 : 2;
+  if (cmax > 1) {
+    int cnt[quasar::kCellBuckets] = {0};
+    int below = 0;
+    for (int i = 0; i < m; i++) cnt[cell_bucket(srt[i])]++;
+    for (int b = 0; b < quasar::kCellBuckets; b++) {
+      cmax = std::max(cmax, cnt[b]);
+      p.cells.base[b] = (uint8_t)below;
+      below += cnt[b];
+    }
+    if (cmax > 3) return;
   }
-  if (cmax > 3) return;
+  p.cells.shift = shift;
   for (int k = 0; k < K; k++)
     for (int b = 1; b <= nb; b++) {
       float tb = t[k * nb + b - 1];
@@ -543,6 +585,7 @@ void int_cells(quasar::IntParams& p, int K, int bits, bool sym, int group) {
       p.cells.tp[k][b - 1] = (uint8_t)((std::lower_bound(srt, srt + m, tb) - srt) + 1);
     }
   for (int i = 0; i < quasar::kCellThr; i++) p.cells.thr[i] = i < m ? srt[i] : NAN;
+  p.cells.split = split;
   p.cells.cpl = cpl;
   p.cells.cmax = cmax;
   // cells count the thresholds at or below u: the unsafe cell is the one

@@ -32,6 +32,15 @@ __device__ __forceinline__ int cell_bucket(float u) {
   return min(max(f, -128), 127) + 128;
 }
 
+// The bucket of u among 512 slices of [-1, 1] whose edges lie where
+// fma(256, u, shift) is an integer: clamp(floor(.), -256, 255) + 256,
+// non-decreasing in u; any u, NaN included, gives an index in [0, 512).
+__device__ __forceinline__ int cell_bucket512(float u, float shift) {
+  int f;
+  asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(f) : "v"(__builtin_fmaf(u, 256.0f, shift)));
+  return min(max(f, -256), 255) + 256;
+}
+
 // ---- bf16 ------------------------------------------------------------------
 // Two fp32 values -> packed bf16 (round to nearest even) in one gfx950
 // instruction (v_cvt_pk_bf16_f32); the low half holds `a`.

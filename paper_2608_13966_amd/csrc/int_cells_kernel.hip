@@ -20,16 +20,32 @@
 // bucket lookup and two LDS additions per weight replace K code evaluations
 // and 3K moment updates.
 //
-// Per weight: u; its bucket among 256 equal slices of [-1, 1] (the host table
-// gives the thresholds below the bucket and the next three thresholds), its
+// Per weight: u; its bucket among 512 slices of [-1, 1] (the host table gives
+// the cell at the bucket's lower edge and the one threshold inside it; grids
+// whose thresholds lie closer take 256 slices and up to three compares), its
 // cell, then h and h w added into the group's cell as exact int64 values
 // (LDS atomics).  A group's lanes are spread over the wavefront (8 apart), so
 // members of one group that hit the same cell do not serialise the atomic.
-// Per group: suffix sums over the cells (each of the L lanes takes a chunk;
-// the chunk totals are combined across lanes with DPP and permlane swaps),
-// then each lane assembles the moments of the clips it owns from NB suffix
-// sums each and solves and scores them exactly as the direct form does
-// (int_common.h).
+// Per group: suffix sums over the cells, in place and in integers (each of
+// the L lanes takes a chunk into registers; the chunk totals are combined
+// across lanes with DPP and permlane swaps), then each lane assembles the
+// moments of the clips it owns from NB suffix sums each and solves and scores
+// them exactly as the direct form does (int_common.h).
+//
+// What bounds it: on the Llama-3.1-8B layer set (INT2 g64, 12 clips, EMA, 14.4
+// bytes per weight) a launch moves 4.9 TB/s, about a plain copy's rate, with
+// the VALU and the LDS each busy two thirds of the time.  Measured steps, all
+// on that set: fp64 suffix sums, rounded cell by cell in two passes over the
+// LDS, and binning and atomics as two loops: 688 us; in integers, one pass in
+// registers, one loop: 638; one compare per weight: 632-642.
+// Forms.  Both sums in a cell (16 bytes) keep four workgroups on a compute
+// unit up to 10 cells a lane.  Beyond that the cells' LDS would leave two: the
+// SPLIT form takes h and then h w through 8-byte cells (each weight's cell is
+// kept, one byte).  INT3 g128 with 15 clips (93 cells), the Llama set: 727 us;
+// both sums at once 1018; the direct kernel 1172.  A form with 8 weights per
+// lane (half the groups per wavefront, so half the LDS) took 750 us there,
+// and 59 against 45 us on the Qwen3-0.6B set (INT3, 8 clips): its per-group
+// work is spread over twice the wavefronts.
 // The emitted codes are recomputed from u with the fp32 recipe, so they are
 // bit-identical to the direct form's.
 #include <type_traits>
@@ -47,41 +63,45 @@ constexpr int N = kIntN;
 // from member j - 1), so that LDS atomics from members of one group that hit
 // the same address do not serialise.
 constexpr bool kSpread = true;
-constexpr int kMemberStride = kSpread ? 8 : 1;
+
+typedef unsigned long long u64;
+
+// x of the lane that DPP control CTRL names (0 where it names none)
+template <int CTRL>
+__device__ __forceinline__ u64 dpp_u64(u64 x) {
+  return ((u64)dpp_u32<CTRL>((uint32_t)(x >> 32)) << 32) | dpp_u32<CTRL>((uint32_t)x);
+}
 
 // The value x of the lane in the paired row (ROWS = 16: rows 0 <-> 1, 2 <-> 3)
 // or half (ROWS = 32), at the same position, for a lane in an even row (the
 // lower half) when `low` is set: the swap leaves the even rows' values in its
 // first result and the odd rows' in its second.
 template <int ROWS>
-__device__ __forceinline__ double paired(double x, bool low) {
-  const uint64_t u = (uint64_t)__double_as_longlong(x);
+__device__ __forceinline__ u64 paired(u64 x, bool low) {
   uint32_t alo, blo, ahi, bhi;
-  swap_rows<ROWS>((uint32_t)u, alo, blo);
-  swap_rows<ROWS>((uint32_t)(u >> 32), ahi, bhi);
-  return low ? __longlong_as_double((long long)(((uint64_t)bhi << 32) | blo))
-             : __longlong_as_double((long long)(((uint64_t)ahi << 32) | alo));
+  swap_rows<ROWS>((uint32_t)x, alo, blo);
+  swap_rows<ROWS>((uint32_t)(x >> 32), ahi, bhi);
+  return low ? ((u64)bhi << 32) | blo : ((u64)ahi << 32) | alo;
 }
 
 // Exclusive suffix sum over the members of a group: member j gets the sum of
-// the values of members j+1 .. L-1.  Members 2i and 2i+1 share a row of 16
-// (8 lanes apart), so member j's suffix is its row partner's value (j even)
-// plus the totals of the later rows, exchanged between rows and halves
-// without LDS.  The values are the chunk totals (integers rounded once to
-// fp64), and the member order of the additions is fixed.
+// the values of members j+1 .. L-1 (integers: exact).  Members 2i and 2i+1
+// share a row of 16 (8 lanes apart), so member j's suffix is its row partner's
+// value (j even) plus the totals of the later rows, exchanged between rows and
+// halves without LDS.
 template <int L>
-__device__ __forceinline__ double members_excl_suffix(double x, int j) {
+__device__ __forceinline__ u64 members_excl_suffix(u64 x, int j) {
   static_assert(kSpread, "members 8 lanes apart");
-  const double nb = dpp_f64<kDppRor8>(x);  // member j ^ 1
-  double e = (j & 1) ? 0.0 : nb;
-  const double r = x + nb;                 // this row's two members
-  const int row = j >> 1;                  // the group's rows in order
-  const double t = paired<16>(r, (row & 1) == 0);
+  const u64 nb = dpp_u64<kDppRor8>(x);  // member j ^ 1
+  u64 e = (j & 1) ? 0ull : nb;
+  const u64 r = x + nb;                 // this row's two members
+  const int row = j >> 1;               // the group's rows in order
+  const u64 t = paired<16>(r, (row & 1) == 0);
   if constexpr (L == 4) {
-    if (row == 0) e += t;
+    e += row == 0 ? t : 0ull;
   } else {
-    const double o = paired<32>(r + t, row < 2);  // the other half's four members
-    e += ((row & 1) ? 0.0 : t) + (row < 2 ? o : 0.0);
+    const u64 o = paired<32>(r + t, row < 2);  // the other half's four members
+    e += ((row & 1) ? 0ull : t) + (row < 2 ? o : 0ull);
   }
   return e;
 }
@@ -92,29 +112,38 @@ __device__ __forceinline__ double members_excl_suffix(double x, int j) {
 // and the low word of 1.5 2^52 is zero.
 constexpr double kMagic = 6755399441055744.0;  // 1.5 * 2^52
 constexpr uint32_t kMagicHi = 0x43380000u;
-__device__ __forceinline__ uint64_t scaled_to_i64(double x, double scale) {
-  const uint64_t b = (uint64_t)__double_as_longlong(__builtin_fma(x, scale, kMagic));
-  return ((uint64_t)((uint32_t)(b >> 32) - kMagicHi) << 32) | (uint32_t)b;
+__device__ __forceinline__ u64 scaled_to_i64(double x, double scale) {
+  const u64 b = (u64)__double_as_longlong(__builtin_fma(x, scale, kMagic));
+  return ((u64)((uint32_t)(b >> 32) - kMagicHi) << 32) | (uint32_t)b;
 }
 // ... and back, correctly rounded: the high word exactly times 2^32 plus the
-// low word, one rounding (sums of the cells reach 2^58)
-__device__ __forceinline__ double i64_to_double(uint64_t n) {
+// low word, one rounding
+__device__ __forceinline__ double i64_to_double(u64 n) {
   return __builtin_fma((double)(int32_t)(uint32_t)(n >> 32), 4294967296.0, (double)(uint32_t)n);
 }
+__device__ __forceinline__ double u64_to_double(u64 n) {
+  return __builtin_fma((double)(uint32_t)(n >> 32), 4294967296.0, (double)(uint32_t)n);
+}
 
-template <bool W_BF16, int EMA, int BITS, int G, bool SYM>
+// SPLIT: a cell holds one int64, and the two sums are taken one after the
+// other in the same LDS (h, then h w); otherwise a cell holds both.
+template <bool W_BF16, int EMA, int BITS, int G, bool SYM, bool SPLIT>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) void int_cells_kernel(IntParams p) {
   constexpr int L = G / N;     // lanes per group
   constexpr int GPW = 64 / L;  // groups per wavefront
   constexpr int QMAX = SYM ? (1 << (BITS - 1)) - 1 : (1 << BITS) - 1;
   constexpr int NB = SYM ? 2 * QMAX : QMAX;  // code steps per clip
   constexpr int OWN = kMaxClips / L;         // clips a lane may own
-  static_assert(kThreads == kCellBuckets && kThreads == kMaxClips * kCellSteps, "one table entry per thread");
+  constexpr int CELL = SPLIT ? 8 : 16;       // bytes
+  constexpr int CMOST = int_cells_most(SPLIT);
+  static_assert(2 * kThreads == kIntBuckets && kThreads == kCellBuckets && kThreads == kMaxClips * kCellSteps, "table entries per thread");
   static_assert((size_t)int_stage_bytes<kSpread, G>() == int_cells_stage_bytes(G), "the launch sizes the stage");
 
-  extern __shared__ __align__(16) double s_hist[];  // [wave][group slot][cell][h, h w], or the store stage
-  __shared__ uint4 s_bucket[kCellBuckets];
-  __shared__ uint8_t s_tp[kMaxClips * kCellSteps];
+  extern __shared__ __align__(16) u64 s_hist[];  // [wave][group slot][cell]{h, h w}, or the store stage
+  // one compare: 512 entries {threshold, cell offset}; more: 256 entries
+  // {cell offset, three thresholds}
+  __shared__ __align__(16) uint4 s_bucket[kThreads];
+  __shared__ __align__(16) uint8_t s_tp[kMaxClips * kCellSteps];
   __shared__ float s_alpha[kMaxClips], s_clip[kMaxClips];
   __shared__ float s_win[kThreads / 64][GPW][4];
 
@@ -123,11 +152,17 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
   const int lane = tid & 63, wave = wave_index();
   const int j = M::member(lane), slot = M::slot(lane);
   const int K = p.n_clips;
+  const int cmax = p.cells.cmax;
 
   {  // the tables, read from the kernel-argument segment with per-lane indices
     const IntCells& cl = kernarg_params<IntParams>()->cells;
-    const int c = cl.base[tid];
-    s_bucket[tid] = make_uint4((uint32_t)c, as_u32(cl.thr[c]), as_u32(cl.thr[c + 1]), as_u32(cl.thr[c + 2]));
+    if (cmax == 1) {
+      const int c0 = cl.base[2 * tid], c1 = cl.base[2 * tid + 1];
+      s_bucket[tid] = make_uint4(as_u32(cl.thr[c0]), (uint32_t)(c0 * CELL), as_u32(cl.thr[c1]), (uint32_t)(c1 * CELL));
+    } else {
+      const int c = cl.base[tid];
+      s_bucket[tid] = make_uint4((uint32_t)(c * CELL), as_u32(cl.thr[c]), as_u32(cl.thr[c + 1]), as_u32(cl.thr[c + 2]));
+    }
     s_tp[tid] = (&cl.tp[0][0])[tid];
   }
   if (tid < kMaxClips) {
@@ -147,7 +182,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
   // this wavefront's LDS: its groups' cells, before that the stage of the
   // EMA's store, and after them the stage of the exact path and of r's store
   const int cpl = p.cells.cpl;
-  double* const s_wave = s_hist + (size_t)wave * (int_cells_wave_bytes(G, cpl) / sizeof(double));
+  const int wave_bytes = (int)int_cells_wave_bytes(G, SPLIT, cpl);
+  u64* const s_wave = s_hist + wave * (wave_bytes / 8);
   const WaveImage im = int_image<L>(s_wave, wave_g0, mtx.n_groups, slot, j, lane);
 
   WRegs<W_BF16> wr;
@@ -156,26 +192,28 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
   const IntRange rg = int_range<L, SYM, W_BF16, kSpread>(wr);
 
   // ---- this group's cells: lane j owns cells [j cpl, (j + 1) cpl) -----------
-  // Groups are int_cells_stride(cpl) cells apart, an odd number, so that the
-  // same cell of the wavefront's groups falls in different LDS banks.  The
-  // wavefront clears its whole area, 16 bytes per lane and step.
-  double* hist = s_wave + (size_t)slot * int_cells_stride<L>(cpl) * 2;
-  double* mine = hist + 2 * j * cpl;
-  {
-    const int n16 = GPW * int_cells_stride<L>(cpl);
+  // Groups are int_cells_stride(L, cpl) cells apart, an odd number, so that the
+  // same cell of the wavefront's groups falls in different LDS banks.
+  const int stride = int_cells_stride(L, cpl);
+  u64* const hist = s_wave + slot * (stride * (CELL / 8));
+  // clear the wavefront's whole area, 16 bytes per lane and step
+  auto clear = [&]() {
+    const int n16 = (GPW * stride * CELL + 15) / 16;
     uint4* z = reinterpret_cast<uint4*>(s_wave);
 #pragma unroll 1
     for (int i = lane; i < n16; i += 64) z[i] = make_uint4(0u, 0u, 0u, 0u);
-  }
+  };
+  clear();
 
   // ---- h and h w of every weight into its cell, as exact integers --------------
   // h and h w are scaled by powers of two that bring the group's largest |h|
   // and |h| max|w| below 2^B, B = 51, rounded to integers and added as int64:
   // every cell sum is exact (below 2^58), whatever the order of the atomics,
-  // and is rounded once to fp64 in the scan.  Clips whose codes agree on the
-  // whole group get bit-identical moments, so their scores tie exactly and the
-  // lowest index wins, as in the exact definition.  A term loses at most
-  // 2^-52 of the largest one; the fit below checks what that can do to it.
+  // and so is every sum over cells; a clip's moments are rounded once each to
+  // fp64.  Clips whose codes agree on the whole group get bit-identical
+  // moments, so their scores tie exactly and the lowest index wins, as in the
+  // exact definition.  A term loses at most 2^-52 of the largest one; the fit
+  // below checks what that can do to it.
   constexpr int B = 51;
   float hmax = 0.0f;
 #pragma unroll
@@ -188,52 +226,79 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
   double Svww = 0.0;
   wave_lds_fence();  // the cells are clear
 
-  // ---- the cell of every weight (four bucket reads in flight at a time) -----
-  // Thresholds outside u's bucket lie on the far side of u and the table's
-  // padding is NaN, so cmax compares never pass the last threshold.
-  uint32_t cells[N / 4];  // four cells per register, one byte each
-  auto bin = [&](auto cmax_tag) {
+  auto add = [&](u64* c, u64 x) {
+    __hip_atomic_fetch_add(c, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+  };
+  // the cell at byte offset `off` of this group
+  auto cell_at = [&](uint32_t off) { return reinterpret_cast<u64*>(reinterpret_cast<char*>(hist) + off); };
+
+  // The cell of a weight: its bucket's first cell plus up to cmax compares
+  // (IntCells).  Thresholds outside u's bucket lie on the far side of u and
+  // the table's padding is NaN, so the compares never pass the last threshold.
+  // Four weights at a time, and their bucket entries are read while the four
+  // before them are added into their cells.  SPLIT: only h is added, and the
+  // cells' offsets (one byte each, in units of 8) are kept for h w.
+  uint32_t cells[SPLIT ? N / 4 : 1];
+  auto fill = [&](auto cmax_tag) {
     constexpr int C = decltype(cmax_tag)::value;
-#pragma unroll
-    for (int c4 = 0; c4 < N / 4; c4++) {
-      float u[4];
-      uint4 e[4];
-#pragma unroll
-      for (int t = 0; t < 4; t++) {
-        u[t] = int_u<SYM>(wr.get(4 * c4 + t), rg);
-        e[t] = s_bucket[cell_bucket(u[t])];
-      }
-      uint32_t packed = 0;
+    float w[4], u[4];
+    typename std::conditional<C == 1, uint2, uint4>::type e[4];
+    auto fetch = [&](int i0) {
 #pragma unroll
       for (int t = 0; t < 4; t++) {
-        uint32_t cell = e[t].x + (u[t] >= as_f32(e[t].y) ? 1u : 0u);
-        if constexpr (C > 1) cell += (u[t] >= as_f32(e[t].z) ? 1u : 0u);
-        if constexpr (C > 2) cell += (u[t] >= as_f32(e[t].w) ? 1u : 0u);
-        packed |= cell << (8 * t);
+        w[t] = wr.get(i0 + t);
+        u[t] = int_u<SYM>(w[t], rg);
+        if constexpr (C == 1)
+          e[t] = reinterpret_cast<const uint2*>(s_bucket)[cell_bucket512(u[t], p.cells.shift)];
+        else
+          e[t] = s_bucket[cell_bucket(u[t])];
       }
-      cells[c4] = packed;
+    };
+    fetch(0);
+#pragma unroll
+    for (int i0 = 0; i0 < N; i0 += 4) {
+      uint32_t off[4];
+      float x[4];
+#pragma unroll
+      for (int t = 0; t < 4; t++) {
+        if constexpr (C == 1) {
+          off[t] = e[t].y + (u[t] >= as_f32(e[t].x) ? CELL : 0u);
+        } else {
+          off[t] = e[t].x + (u[t] >= as_f32(e[t].y) ? CELL : 0u) + (u[t] >= as_f32(e[t].z) ? CELL : 0u);
+          if constexpr (C > 2) off[t] += (u[t] >= as_f32(e[t].w) ? CELL : 0u);
+        }
+        x[t] = w[t];
+      }
+      if (i0 + 4 < N) fetch(i0 + 4);
+#pragma unroll
+      for (int t = 0; t < 4; t++) {
+        // opaque: the conversions are the same in every copy of this loop, and
+        // would otherwise be made for all N weights before the branch on cmax
+        float vi = v[i0 + t];
+        asm volatile("" : "+v"(vi));
+        const double V = (double)vi;
+        u64* c = cell_at(off[t]);
+        add(c, scaled_to_i64(V, sh));
+        if constexpr (!SPLIT) {
+          const double Wd = (double)x[t];
+          const double VW = V * Wd;
+          Svww = __builtin_fma(VW, Wd, Svww);
+          add(c + 1, scaled_to_i64(VW, shw));
+        }
+      }
+      if constexpr (SPLIT) {
+        static_assert(CELL == 8, "offsets in units of 8 fit a byte each");
+        cells[i0 / 4] = (off[0] >> 3) | (off[1] << 5) | (off[2] << 13) | (off[3] << 21);
+      }
       __builtin_amdgcn_sched_barrier(0);
     }
   };
-  const int cmax = p.cells.cmax;
   if (cmax == 1)
-    bin(std::integral_constant<int, 1>{});
+    fill(std::integral_constant<int, 1>{});
   else if (cmax == 2)
-    bin(std::integral_constant<int, 2>{});
+    fill(std::integral_constant<int, 2>{});
   else
-    bin(std::integral_constant<int, 3>{});
-
-  // ---- h and h w of every weight into its cell --------------------------------
-#pragma unroll
-  for (int i = 0; i < N; i++) {
-    const int cell = (int)((cells[i >> 2] >> (8 * (i & 3))) & 0xffu);
-    const double V = (double)v[i], Wd = (double)wr.get(i);
-    const double VW = V * Wd;
-    Svww = __builtin_fma(VW, Wd, Svww);
-    uint64_t* c64 = reinterpret_cast<uint64_t*>(hist + 2 * cell);
-    __hip_atomic_fetch_add(c64, scaled_to_i64(V, sh), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-    __hip_atomic_fetch_add(c64 + 1, scaled_to_i64(VW, shw), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-  }
+    fill(std::integral_constant<int, 3>{});
   wave_lds_fence();
 
   // A weight among merged thresholds (rare) lies in the unsafe cell, where the
@@ -241,91 +306,163 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
   // unless its saliency is 0 (h >= 0, so the cell's sum of h is 0 exactly when
   // every weight in it has h = 0, and those weights add nothing to any moment).
   const int ucell = p.cells.unsafe_cell;
-  // (read with the suffix pass's access type, which then cannot move above it)
-  const bool group_unsafe = ucell >= 0 && reinterpret_cast<const ulonglong2*>(hist)[ucell].x != 0;
+  const bool group_unsafe = ucell >= 0 && hist[ucell * (CELL / 8)] != 0;
+  wave_lds_fence();  // read before the sums are taken in place
 
-  // ---- suffix sums over the cells (exact integer cells, rounded once to fp64):
-  // the chunk totals first, then the members above this one, then a second
-  // pass that writes the suffix sums.  The lane's cells are read four at a
-  // time, all four reads in flight before the first is used; an index past
-  // the lane's last cell reads that cell again and contributes nothing, and
-  // in the second pass (from the top down) its write to that cell comes
-  // before the cell's own.
-  {
-    // one access type for the reads and the writes: the writes may not be
-    // moved above reads of the same cell
-    ulonglong2* mc = reinterpret_cast<ulonglong2*>(mine);
-    uint64_t ih = 0, iw = 0;  // exact integer chunk totals
-#pragma unroll 1
-    for (int b = 0; b < cpl; b += 4) {
-      ulonglong2 t[4];
+  // ---- suffix sums over the cells, in place and in integers: the lane's
+  // cells are read into registers (a compile-time count, the host rounds cpl
+  // up to it; the cells past the last threshold are zero), summed from the
+  // top down, and the total of the members above this one added.
+  auto suffix = [&](auto cpl_tag) {
+    constexpr int C = decltype(cpl_tag)::value;
+    if constexpr (SPLIT) {
+      u64* mc = hist + j * C;
+      u64 t[C];
 #pragma unroll
-      for (int c = 0; c < 4; c++) t[c] = mc[min(b + c, cpl - 1)];
+      for (int c = 0; c < C; c++) t[c] = mc[c];
 #pragma unroll
-      for (int c = 0; c < 4; c++) {
-        const bool in = b + c < cpl;
-        ih += in ? t[c].x : 0ull;
-        iw += in ? t[c].y : 0ull;
+      for (int c = C - 2; c >= 0; c--) t[c] += t[c + 1];
+      const u64 x = members_excl_suffix<L>(t[0], j);
+#pragma unroll
+      for (int c = 0; c < C; c++) mc[c] = t[c] + x;
+    } else {
+      ulonglong2* mc = reinterpret_cast<ulonglong2*>(hist) + j * C;
+      ulonglong2 t[C];
+#pragma unroll
+      for (int c = 0; c < C; c++) t[c] = mc[c];
+#pragma unroll
+      for (int c = C - 2; c >= 0; c--) {
+        t[c].x += t[c + 1].x;
+        t[c].y += t[c + 1].y;
       }
+      const u64 xh = members_excl_suffix<L>(t[0].x, j), xw = members_excl_suffix<L>(t[0].y, j);
+#pragma unroll
+      for (int c = 0; c < C; c++) mc[c] = make_ulonglong2(t[c].x + xh, t[c].y + xw);
     }
-    double eh2 = members_excl_suffix<L>(i64_to_double(ih), j), ew2 = members_excl_suffix<L>(i64_to_double(iw), j);
-#pragma unroll 1
-    for (int b = (cpl - 1) & ~3; b >= 0; b -= 4) {
-      ulonglong2 t[4];
+  };
+  auto suffix_sums = [&]() {
+    if constexpr (SPLIT) {
+      if (cpl <= 12)
+        suffix(std::integral_constant<int, 12>{});
+      else if (cpl == 14)
+        suffix(std::integral_constant<int, 14>{});
+      else
+        suffix(std::integral_constant<int, 16>{});
+    } else {
+      if (cpl == 2)
+        suffix(std::integral_constant<int, 2>{});
+      else if (cpl == 4)
+        suffix(std::integral_constant<int, 4>{});
+      else if (cpl == 6)
+        suffix(std::integral_constant<int, 6>{});
+      else if (cpl == 8)
+        suffix(std::integral_constant<int, 8>{});
+      else
+        suffix(std::integral_constant<int, 10>{});
+    }
+    wave_lds_fence();
+  };
+  suffix_sums();
+
+  // ---- the clips this lane owns, k = j + L t: moments from NB suffix sums, in
+  // integers.  From the highest step down, R is the sum of the P_b so far and
+  // S the sum of the R: sum_b b P_b, so sum_b (2b - 1) P_b = 2 S - R.  P_b <=
+  // 2^58, so 7 steps keep S below 2^63; with 14 or 15 steps the upper ones are
+  // summed on their own: sum_{b > 8} b P_b = S_hi + 8 R_hi.
+  double A0[OWN], A1[OWN], A2[OWN];
+  auto steps = [&](int k, auto&& f) {  // f(b, cell) for b = NB .. 1
+    const uint4 tw4 = *reinterpret_cast<const uint4*>(s_tp + k * kCellSteps);
+    const uint32_t tw[4] = {tw4.x, tw4.y, tw4.z, tw4.w};
 #pragma unroll
-      for (int c = 0; c < 4; c++) t[c] = mc[min(b + c, cpl - 1)];
+    for (int b = NB; b >= 1; b--) f(b, (int)((tw[(b - 1) >> 2] >> (8 * ((b - 1) & 3))) & 0xffu));
+  };
+  u64 tot_h, tot_w;  // the whole group's sums: cell 0's suffix
 #pragma unroll
-      for (int c = 3; c >= 0; c--) {
-        const bool in = b + c < cpl;
-        eh2 += in ? i64_to_double(t[c].x) : 0.0;
-        ew2 += in ? i64_to_double(t[c].y) : 0.0;
-        mc[min(b + c, cpl - 1)] = make_ulonglong2((unsigned long long)__double_as_longlong(eh2),
-                                                  (unsigned long long)__double_as_longlong(ew2));
+  for (int t = 0; t < OWN; t++) {
+    A0[t] = A1[t] = A2[t] = 0.0;
+    const int k = j + L * t;
+    if (k < K) {
+      u64 R = 0, S = 0, Q = 0, Rhi = 0, Shi = 0;
+      steps(k, [&](int b, int c) {
+        if constexpr (SPLIT) {
+          R += hist[c];
+        } else {
+          const ulonglong2 s = reinterpret_cast<const ulonglong2*>(hist)[c];
+          R += s.x;
+          Q += s.y;
+        }
+        S += R;
+        if (b == 9) {
+          Rhi = R;
+          Shi = S;
+          R = S = 0;
+        }
+      });
+      A0[t] = u64_to_double(R);
+      A1[t] = __builtin_fma(2.0, u64_to_double(S), -A0[t]);
+      if constexpr (NB > 8) {
+        const double rh = u64_to_double(Rhi);
+        A1[t] += __builtin_fma(2.0, u64_to_double(Shi), 15.0 * rh);
+        A0[t] += rh;
       }
+      A2[t] = i64_to_double(Q);
     }
   }
-  wave_lds_fence();
+  tot_h = hist[0];
+  if constexpr (!SPLIT) {
+    tot_w = hist[1];
+  } else {
+    // h w through the same cells
+    wave_lds_fence();
+    clear();
+    wave_lds_fence();
+#pragma unroll
+    for (int i = 0; i < N; i++) {
+      const double V = (double)v[i], Wd = (double)wr.get(i);
+      const double VW = V * Wd;
+      Svww = __builtin_fma(VW, Wd, Svww);
+      add(hist + ((cells[i / 4] >> (8 * (i & 3))) & 0xffu), scaled_to_i64(VW, shw));
+      if (i % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+    }
+    wave_lds_fence();
+    suffix_sums();
+#pragma unroll
+    for (int t = 0; t < OWN; t++) {
+      const int k = j + L * t;
+      if (k < K) {
+        u64 Q = 0;
+        steps(k, [&](int, int c) { Q += hist[c]; });
+        A2[t] = i64_to_double(Q);
+      }
+    }
+    tot_w = hist[0];
+  }
 
   // back from the integer scale (exact: powers of two)
   const double rsh = __builtin_amdgcn_ldexp(1.0, eh - B), rshw = __builtin_amdgcn_ldexp(1.0, eh + ew - B);
   IntMoments mo;
-  {
-    const double2 tot = *reinterpret_cast<const double2*>(hist);  // cell 0's suffix: the whole group
-    mo.Sv = tot.x * rsh;
-    mo.Svw = tot.y * rshw;
-  }
+  mo.Sv = u64_to_double(tot_h) * rsh;
+  mo.Svw = i64_to_double(tot_w) * rshw;
   mo.Svww = M::sum(Svww);
   mo.thr = 1e-12 * mo.Sv * mo.Sv * (double)QMAX * (double)QMAX;
   mo.rSv = rcp_f64(mo.Sv);
   // each term of sum h and of sum h w is off by at most half a unit of its
-  // fixed point; the sums and the fit's products carry fp64 roundings
+  // fixed point; the moments and the fit's products carry fp64 roundings
   mo.qh = 0.5 * (double)G * rsh;
   mo.qhw = 0.5 * (double)G * rshw;
   mo.rel = 0x1p-47;
   mo.wabs = (double)wabs;
   int_fit_bounds<QMAX>(mo);
-
-  // ---- the clips this lane owns: moments from NB suffix sums ------------------
-  auto moments = [&](int k, double& A0, double& A1, double& A2) {
-    A0 = A1 = A2 = 0.0;
-    const uint4 tw4 = *reinterpret_cast<const uint4*>(s_tp + k * kCellSteps);
-    const uint32_t tw[4] = {tw4.x, tw4.y, tw4.z, tw4.w};
 #pragma unroll
-    for (int b = 1; b <= NB; b++) {
-      const int c = (int)((tw[(b - 1) >> 2] >> (8 * ((b - 1) & 3))) & 0xffu);
-      const double2 s = *reinterpret_cast<const double2*>(hist + 2 * c);
-      A0 += s.x;
-      A1 = __builtin_fma((double)(2 * b - 1), s.x, A1);
-      A2 += s.y;
-    }
-    A0 *= rsh;
-    A1 *= rsh;
-    A2 *= rshw;
+  for (int t = 0; t < OWN; t++) {
+    A0[t] *= rsh;
+    A1[t] *= rsh;
+    A2[t] *= rshw;
     if constexpr (SYM) {  // q = n - Q
-      A1 = __builtin_fma((double)QMAX * (double)QMAX, mo.Sv, __builtin_fma(-2.0 * (double)QMAX, A0, A1));
-      A2 = __builtin_fma(-(double)QMAX, mo.Svw, A2);
+      A1[t] = __builtin_fma((double)QMAX * (double)QMAX, mo.Sv, __builtin_fma(-2.0 * (double)QMAX, A0[t], A1[t]));
+      A2[t] = __builtin_fma(-(double)QMAX, mo.Svw, A2[t]);
     }
-  };
+  }
 
   // Selection.  With fp32 (s, z) the candidate's score is that of its exact
   // fit up to the fp32 rounding of (s, z), a relative 1e-12 or so; the exact
@@ -333,29 +470,28 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
   // D = Sv A1 - A0^2; symmetric: C - A2^2 / A1), with C the same for every
   // clip.  So each lane ranks its clips by num^2 / D (cross-multiplied, ties
   // to the lowest index), fits and scores only its best one, and the group's
-  // argmin runs over keys made from D / num^2.  Groups with a clip whose fit
-  // degenerates (no saliency, all of it on one code), and deployed
-  // precisions other than fp32, score every clip (int_fit_score).  A group
-  // with a clip whose fit the moments cannot fix accurately enough
-  // (int_fit_ill), or with a weight among merged thresholds, evaluates every
-  // clip straight from its weights (int_exact_all).
+  // argmin runs over keys made from D / num^2.
+  // Groups with a clip whose fit degenerates (no saliency, all of it on one
+  // code), and deployed precisions other than fp32, score every clip
+  // (int_fit_score).  A group with a clip whose fit the moments cannot fix
+  // accurately enough (int_fit_ill), or with a weight among merged
+  // thresholds, evaluates every clip straight from its weights
+  // (int_exact_wave).
   IntBest best = int_best_init();
   bool full = p.param_dtype != 0;
   bool ill = group_unsafe;
   int bk = -1;
-  double bn = 0.0, bd = 1.0;
+  double bn = 0.0, bd = 1.0, b0 = 0.0, b1 = 0.0, b2 = 0.0;
   if (!full && !group_unsafe) {
-    // unrolled: the clips' LDS reads and fp64 chains interleave
+    // unrolled: the clips' fp64 chains interleave
 #pragma unroll
     for (int t = 0; t < OWN; t++) {
       const int k = j + L * t;
       if (k < K) {
-        double A0, A1, A2;
-        moments(k, A0, A1, A2);
-        ill |= int_fit_ill<SYM, QMAX>(mo, A0, A1, A2);
-        const double D = SYM ? A1 : mo.Sv * A1 - A0 * A0;
-        const double num = SYM ? A2 : mo.Sv * A2 - A0 * mo.Svw;
-        const bool degenerate = SYM ? (A1 == 0.0) : (mo.Sv == 0.0 || D <= mo.thr);
+        ill |= int_fit_ill<SYM, QMAX>(mo, A0[t], A1[t], A2[t]);
+        const double D = SYM ? A1[t] : mo.Sv * A1[t] - A0[t] * A0[t];
+        const double num = SYM ? A2[t] : mo.Sv * A2[t] - A0[t] * mo.Svw;
+        const bool degenerate = SYM ? (A1[t] == 0.0) : (mo.Sv == 0.0 || D <= mo.thr);
         const double n2 = num * num;
         if (degenerate) {
           full = true;
@@ -363,6 +499,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
           bk = k;
           bn = n2;
           bd = D;
+          b0 = A0[t];
+          b1 = A1[t];
+          b2 = A2[t];
         }
       }
     }
@@ -370,19 +509,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
   ill = M::max(ill ? 1.0f : 0.0f) > 0.0f;
   if (!ill) {
     if (M::max(full ? 1.0f : 0.0f) > 0.0f) {
-#pragma unroll 1
+#pragma unroll
       for (int t = 0; t < OWN; t++) {
         const int k = j + L * t;
-        if (k < K) {
-          double A0, A1, A2;
-          moments(k, A0, A1, A2);
-          int_fit_score<SYM, QMAX>(p, k, s_clip[k], rg, mo, A0, A1, A2, best);
-        }
+        if (k < K) int_fit_score<SYM, QMAX>(p, k, s_clip[k], rg, mo, A0[t], A1[t], A2[t], best);
       }
       ill = M::max(best.ill ? 1.0f : 0.0f) > 0.0f;
     } else if (bk >= 0) {
-      double b0, b1, b2;
-      moments(bk, b0, b1, b2);
       int_fit_score<SYM, QMAX>(p, bk, s_clip[bk], rg, mo, b0, b1, b2, best);
       // rank by D / num^2 (num = 0: the worst fit, kept finite)
       best.key = make_key(fmin(bd * rcp_f64(bn), 1e300), bk);
@@ -413,23 +546,31 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
                                          active);
 }
 
-template <bool W_BF16, int EMA, int BITS, int G>
-hipError_t launch_g(const IntParams& p, hipStream_t s) {
+template <bool W_BF16, int EMA, int BITS, int G, bool SPLIT>
+hipError_t launch_s(const IntParams& p, hipStream_t s) {
   constexpr int64_t groups_per_block = int_units_per_block(G);
   const int64_t blocks =
       p.batch.n > 1 ? p.batch.total_blocks : (p.n_groups + groups_per_block - 1) / groups_per_block;
-  const size_t lds = int_cells_lds_bytes(G, p.cells.cpl);
+  const size_t lds = int_cells_lds_bytes(G, SPLIT, p.cells.cpl);
   const dim3 grid((unsigned)blocks), block(kThreads);
   if (p.symmetric) {
     if constexpr (EMA <= 2) {
-      hipLaunchKernelGGL((int_cells_kernel<W_BF16, EMA, BITS, G, true>), grid, block, lds, s, p);
+      hipLaunchKernelGGL((int_cells_kernel<W_BF16, EMA, BITS, G, true, SPLIT>), grid, block, lds, s, p);
       return hipGetLastError();
     } else {
       return hipErrorInvalidValue;
     }
   }
-  hipLaunchKernelGGL((int_cells_kernel<W_BF16, EMA, BITS, G, false>), grid, block, lds, s, p);
+  hipLaunchKernelGGL((int_cells_kernel<W_BF16, EMA, BITS, G, false, SPLIT>), grid, block, lds, s, p);
   return hipGetLastError();
+}
+
+template <bool W_BF16, int EMA, int BITS, int G>
+hipError_t launch_g(const IntParams& p, hipStream_t s) {
+  if constexpr (BITS > 2) {  // INT2 grids have at most 46 cells
+    if (p.cells.split) return launch_s<W_BF16, EMA, BITS, G, true>(p, s);
+  }
+  return launch_s<W_BF16, EMA, BITS, G, false>(p, s);
 }
 
 template <bool W_BF16, int EMA, int BITS>

@@ -77,43 +77,48 @@ __device__ __forceinline__ const MatrixSlot& batch_slot(int64_t& blk) {
 // the distinct T(k, b) of all clips, and the cell of u is #{i : t_i <= u}.
 constexpr int kCellBuckets = 256;  // equal slices of u in [-1, 1] (cell_bucket in device_common.h)
 constexpr int kCellSteps = 16;     // >= NB (15 at most), bytes per clip in tp
-constexpr int kCellsPerLane = 15;  // most cells a lane scans (LDS <= 60 KB)
-constexpr int kCellsPerLaneAuto = 10;  // most for which the binned kernel is the default
+constexpr int kIntBuckets = 512;   // ... and of the one-compare table of the binned INT kernel
+// Cells a lane scans, rounded up to a count the kernel has code for, and the
+// most it may be.  split: a cell holds one sum at a time.
+constexpr int int_cells_most(bool split) { return split ? 16 : 10; }
+constexpr int int_cells_round(bool split, int cpl) { return split && cpl < 12 ? 12 : (cpl + 1) & ~1; }
 constexpr int kCellThr = 136;      // >= 128 (the search range) and >= M + 3
 struct IntCells {
   int n_cells;  // M + 1; 0 = use the direct kernel
+  int split;    // 1: the kernel's SPLIT form (one sum at a time in the cells)
   int cpl;      // cells per lane: the group's L lanes scan L * cpl >= M + 1 cells
   int cmax;     // compares per weight, 1 .. 3
   // the cell of the u among merged thresholds, where the cell does not fix
   // every clip's code (-1: none); a group with saliency in it has its moments
   // summed directly
   int unsafe_cell;
-  // per bucket b = clamp(floor(128 u), -128, 127) + 128: for u in the
-  // bucket the cell is base plus the number of t_base .. t_base+cmax-1 at
-  // or below u
-  uint8_t base[kCellBuckets];
+  // The bucket b of u: cmax = 1: clamp(floor(fma(256, u, shift)), -256, 255) +
+  // 256; else clamp(floor(128 u), -128, 127) + 128.  For u in the bucket the
+  // cell is base plus the number of t_base .. t_base+cmax-1 at or below u.
+  float shift;
+  uint8_t base[kIntBuckets];
   uint8_t tp[kMaxClips][kCellSteps];  // [k][b - 1]: first cell with u >= T(k, b)
   float thr[kCellThr];                // t_0 .. t_{M-1}, then NaN
 };
 
 // Cells between consecutive groups of the binned kernel: the L * cpl cells a
 // group scans, rounded up to an odd count so that the same cell of different
-// groups lands in different LDS banks (a cell is 16 bytes, four banks).
-template <int L>
-__host__ __device__ constexpr int int_cells_stride(int cpl) { return (L * cpl) | 1; }
+// groups lands in different LDS banks (a cell is four banks, split two).
+__host__ __device__ constexpr int int_cells_stride(int L, int cpl) { return (L * cpl) | 1; }
 
 // LDS of one wavefront of the binned kernel: 64 / L groups' cells (h and h w
-// in fp64 per cell), or, where that is less, the stage of its coalesced
-// stores (a 1024-element fp32 stretch plus one 16-byte pad per group).
-constexpr size_t int_cells_stage_bytes(int group) { return (size_t)(256 + 1024 / group) * 16; }
-constexpr size_t int_cells_wave_bytes(int group, int cpl) {
-  const size_t cells = (size_t)(64 / (group / 16)) *
-                       (size_t)(group == 64 ? int_cells_stride<4>(cpl) : int_cells_stride<8>(cpl)) * 16;
+// as int64 per cell, split one of them), or, where that is less, the stage of
+// its coalesced stores (a 1024-element fp32 stretch plus one 16-byte pad per
+// group).
+__host__ __device__ constexpr size_t int_cells_stage_bytes(int group) { return (size_t)(256 + 1024 / group) * 16; }
+__host__ __device__ constexpr size_t int_cells_wave_bytes(int group, bool split, int cpl) {
+  const int L = group / 16;
+  const size_t cells = (size_t)(64 / L) * (size_t)int_cells_stride(L, cpl) * (split ? 8 : 16);
   return cells > int_cells_stage_bytes(group) ? cells : int_cells_stage_bytes(group);
 }
 // ... and of one workgroup
-constexpr size_t int_cells_lds_bytes(int group, int cpl) {
-  return (size_t)(kThreads / 64) * int_cells_wave_bytes(group, cpl);
+constexpr size_t int_cells_lds_bytes(int group, bool split, int cpl) {
+  return (size_t)(kThreads / 64) * int_cells_wave_bytes(group, split, cpl);
 }
 
 // Per-call parameters of the INT-b kernels (passed by value as the kernel argument).

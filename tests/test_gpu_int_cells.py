@@ -1,0 +1,60 @@
+"""The forms of the binned INT kernel against the oracle at the edges of their
+tables: few and many cells (both sums of a cell at once, or one after the
+other), grids whose thresholds need one, two or three compares per weight,
+both group sizes and ragged row counts."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2608_13966_amd import quasar as Q
+from paper_2608_13966_amd import synth
+from tests.test_gpu_parity import int_path, run_case
+
+pytestmark = pytest.mark.gpu
+
+# (fmt, bits, group, clips): the cells a group has, and what is at its edge
+GRIDS = [
+    ("int", 2, 64, (1.0,)),                                # 4 cells, the fewest
+    ("int_sym", 2, 128, tuple(synth.clip_grid(1.0, 0.9, 16))),  # no tie cells; dense: several compares
+    ("int", 2, 64, tuple(synth.clip_grid(1.0, 0.3, 16))),  # 35 cells, 10 a lane
+    ("int", 3, 64, tuple(synth.clip_grid(1.0, 0.65, 8))),  # 52 cells: one sum at a time, 14 a lane
+    ("int", 3, 64, tuple(synth.clip_grid(1.0, 0.5, 9))),   # 58 cells, 16 a lane: the most for g64
+    ("int", 3, 128, tuple(synth.clip_grid(1.0, 0.6, 11))),  # 70 cells: the last with both sums at once
+    ("int", 3, 128, tuple(synth.clip_grid(1.0, 0.6, 13))),  # 82 cells: the first with one, 12 a lane
+    ("int", 3, 128, tuple(synth.PAPER_CLIPS)),             # exact-arithmetic ties between clips: two compares
+    ("int", 3, 128, (1.0, 1.0, 0.5, 0.5, 0.25, 0.25, 0.75, 0.75, 0.375)),  # equal and doubled factors
+    ("int", 3, 128, tuple(synth.clip_grid(1.0, 0.3, 16))),  # 100 cells
+    ("int", 4, 128, tuple(synth.clip_grid(1.0, 0.65, 8))),  # 114 cells, 16 a lane, 15 steps
+    ("int_sym", 4, 128, tuple(synth.clip_grid(1.0, 0.65, 9))),  # 127 cells, the most for g128, 14 steps
+]
+
+
+@pytest.mark.parametrize("fmt,bits,group,clips", GRIDS)
+@pytest.mark.parametrize("w_bf16,ema,rows", [(True, True, 5), (False, False, 1)])
+def test_binned_forms(fmt, bits, group, clips, w_bf16, ema, rows):
+    """Random groups, and groups of range [-1, 1] (u = w exactly) whose weights
+    sit on the code thresholds of every clip and one and two floats to either
+    side, where the cell decides the codes."""
+    cols = 3 * group
+    with int_path("binned"):
+        d = Q.Descriptor(rows, cols, fmt=fmt, bits=bits, group=group, clips=clips)
+        assert Q.quasar_int_path(d) == 1
+    name = f"cells.{fmt}{bits}.g{group}.K{len(clips)}.{'bf16' if w_bf16 else 'f32'}"
+    run_case(name, rows, cols, 77, fmt=fmt, bits=bits, group=group, clips=clips, w_bf16=w_bf16, ema=ema)
+    qm = (1 << (bits - 1)) - 1 if fmt == "int_sym" else (1 << bits) - 1
+    pts = [0.0]
+    for f in np.asarray(clips, dtype=np.float32):
+        for b in range(1, (2 * qm if fmt == "int_sym" else qm) + 1):
+            t = (b - qm - 0.5) * f / qm if fmt == "int_sym" else (b - qm / 2 - 0.5) * 2 * f / qm
+            x = lo = hi = np.float32(t)
+            for _ in range(2):
+                lo, hi = np.nextafter(lo, np.float32(-2)), np.nextafter(hi, np.float32(2))
+                pts += [lo, hi]
+            pts.append(x)
+    pts = np.asarray(pts, dtype=np.float32)
+    rng = np.random.default_rng(5)
+    W = rng.choice(pts, size=(8, cols)).astype(np.float32)
+    W[:, ::group], W[:, 1::group] = -1.0, 1.0
+    Wt = torch.from_numpy(W).cuda()
+    v = torch.from_numpy(np.exp(rng.standard_normal(W.shape) * 3).astype(np.float32)).cuda()
+    run_case(name + ".thresholds", *W.shape, 0, fmt=fmt, bits=bits, group=group, clips=clips, w_bf16=False, W=Wt, v=v)
