@@ -214,26 +214,6 @@ void rubin_clip_tables(const quasar_desc* d, quasar::RubinParams& p) {
   }
 }
 
-// The code of u under a clip with scale alpha, in the kernels' fp32 recipe:
-// clamp(rint(fma(u, alpha, 3.5)), 0, 7) (correctly rounded fma, ties to even).
-int rubin_code(float u, float alpha) {
-  const float x = rintf(fmaf(u, alpha, 3.5f));
-  return (int)fminf(fmaxf(x, 0.0f), 7.0f);
-}
-
-// fp32 values in increasing order <-> unsigned keys in increasing order
-uint32_t f32_order_key(float f) {
-  uint32_t u;
-  memcpy(&u, &f, 4);
-  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-}
-float f32_from_order_key(uint32_t k) {
-  const uint32_t u = (k & 0x80000000u) ? (k & 0x7fffffffu) : ~k;
-  float f;
-  memcpy(&f, &u, 4);
-  return f;
-}
-
 // Lay the sorted list out as an implicit binary search tree (node n's children
 // at 2n and 2n + 1) by an in-order walk.
 void eytzinger_fill(float* tree, const float* sorted, int& next, int node) {
@@ -365,37 +345,39 @@ bool rubin_buckets(quasar::RubinParams& p, const float* t, int K) {
   return true;
 }
 
-// The Rubin kernel's code thresholds: the code is non-decreasing in u, so
-// T(k, b) = min{u : code_k(u) >= b + 1} is found by bisection over the
-// ordered fp32 values between -inf (code 0) and +inf (code 7).
+// The least fp32 u with rint(fl(u alpha + c)) >= q, for fl the rounding to
+// fp32 (one rounding: an fma; c = 0: a product) and ties to even throughout,
+// c a multiple of 1/2 and |c|, |q| <= 16: the kernels' code recipes, rint of
+// fma(u, alpha, qmax/2) or, symmetric, of u * alpha (the clamps to the range of
+// codes change nothing at 1 .. qmax, symmetric -Q + 1 .. Q).
+//
+// rint reaches q from x = q - 1/2 if q is even (the tie goes up), else from
+// the next float; call that X.  fl(y) >= X for a real y exactly when y lies
+// above the midpoint of X and the float below it, or at it if X's mantissa is
+// even.  So u is the least float with u alpha + c > or >= that midpoint:
+// midpoint - c is exact in fp64, and so is u alpha (24 x 24 bits), so the
+// quotient needs one neighbour to either side at most.
+float code_threshold(float alpha, float c, int q) {
+  float X = (float)q - 0.5f;
+  if (q & 1) X = nextafterf(X, INFINITY);
+  uint32_t bits;
+  memcpy(&bits, &X, 4);
+  const double y = 0.5 * ((double)X + (double)nextafterf(X, -INFINITY)) - (double)c;
+  const double a = (double)alpha;
+  auto reaches = [&](float u) { return (bits & 1) ? (double)u * a > y : (double)u * a >= y; };
+  float u = (float)(y / a);
+  while (!reaches(u)) u = nextafterf(u, INFINITY);
+  for (float d = nextafterf(u, -INFINITY); reaches(d); d = nextafterf(u, -INFINITY)) u = d;
+  return u;
+}
+
+// The Rubin kernel's code thresholds: T(k, b) = min{u : code_k(u) >= b + 1}
+// (the code is non-decreasing in u).
 void rubin_thresholds(quasar::RubinParams& p, int K) {
   float t[quasar::kRubinThresholds];
   int n = 0;
-  for (int k = 0; k < K; k++) {
-    for (int b = 0; b < 7; b++) {
-      // bracket: around the threshold of exact arithmetic, (b - 3) / alpha,
-      // widened until it holds (else the whole range)
-      const double center = (b - 3.0) / (double)p.alpha[k];
-      uint32_t lo = f32_order_key(-INFINITY), hi = f32_order_key(INFINITY);
-      for (double half = 1e-6; half < 4.0; half *= 16.0) {
-        const uint32_t a = f32_order_key((float)(center - half)), z = f32_order_key((float)(center + half));
-        if (rubin_code(f32_from_order_key(a), p.alpha[k]) < b + 1 &&
-            rubin_code(f32_from_order_key(z), p.alpha[k]) >= b + 1) {
-          lo = a;
-          hi = z;
-          break;
-        }
-      }
-      while (hi - lo > 1) {
-        const uint32_t mid = lo + (hi - lo) / 2;
-        if (rubin_code(f32_from_order_key(mid), p.alpha[k]) >= b + 1)
-          hi = mid;
-        else
-          lo = mid;
-      }
-      t[n++] = f32_from_order_key(hi);
-    }
-  }
+  for (int k = 0; k < K; k++)
+    for (int b = 0; b < 7; b++) t[n++] = code_threshold(p.alpha[k], 3.5f, b + 1);
   if (rubin_buckets(p, t, K)) return;
   // the tree form: every threshold (repeats included) plus the extra
   // boundaries; a weight's cell is the number of them at or below u
@@ -421,19 +403,6 @@ void rubin_thresholds(quasar::RubinParams& p, int K) {
   int next = 0;
   eytzinger_fill(p.thr, sorted, next, 1);
   p.thr[0] = INFINITY;
-}
-
-// The code of u under clip k of an INT-b group, in the kernels' fp32 recipe:
-// asymmetric clamp(rint(fma(u, alpha, qmax/2)), 0, qmax), symmetric
-// clamp(rint(u * alpha), -Q, Q) (correctly rounded fma and product, ties to
-// even).
-int int_code(float u, float alpha, int qmax, bool sym) {
-  if (sym) {
-    const float x = rintf(u * alpha);
-    return (int)fminf(fmaxf(x, -(float)qmax), (float)qmax);
-  }
-  const float x = rintf(fmaf(u, alpha, 0.5f * (float)qmax));
-  return (int)fminf(fmaxf(x, 0.0f), (float)qmax);
 }
 
 // The bucket of a finite u in the binned kernel, in its fp32 recipe:
@@ -473,21 +442,24 @@ bool int_one_compare(uint8_t* base, const float* s, int m, float shift) {
   auto bucket = [&](float u) {
     return (int)fminf(fmaxf(floorf(fmaf(u, 256.0f, shift)), -256.0f), 255.0f) + 256;
   };
-  int i = 0;
-  for (int b = 0; b < quasar::kIntBuckets; b++) {
-    while (i < m && bucket(s[i]) == b && bucket(nextafterf(s[i], -INFINITY)) < b) i++;
-    base[b] = (uint8_t)i;
-    int inside = 0;
-    for (; i < m && bucket(s[i]) == b; i++) inside++;
-    if (inside > 1) return false;
+  int next = 0;    // buckets below it are filled
+  int inside = -1;  // the bucket of the last threshold inside one
+  for (int i = 0; i < m; i++) {
+    const int b = bucket(s[i]);
+    for (; next <= b; next++) base[next] = (uint8_t)i;
+    if (bucket(nextafterf(s[i], -INFINITY)) < b) {
+      base[b] = (uint8_t)(i + 1);  // its least u: the sorted list's first threshold in b
+    } else {
+      if (inside == b) return false;
+      inside = b;
+    }
   }
+  for (; next < quasar::kIntBuckets; next++) base[next] = (uint8_t)m;
   return true;
 }
 
 // The binned INT kernel's tables for this clip grid (int_cells_kernel.hip):
-// every threshold T(k, b) = the least fp32 u with code_k(u) >= q0 + b, found
-// by bisection over the ordered fp32 values between -inf (the lowest code)
-// and +inf (the highest).  Leaves n_cells = 0 -- the direct kernel runs --
+// every threshold T(k, b) = the least fp32 u with code_k(u) >= q0 + b.  Leaves n_cells = 0 -- the direct kernel runs --
 // when int_cells_fit says so, when a bucket needs more than three compares, or
 // when QUASAR_INT_PATH=direct is set.  QUASAR_INT_PATH=binned takes the binned
 // kernel wherever its tables fit.
@@ -517,28 +489,7 @@ void int_cells(quasar::IntParams& p, int K, int bits, bool sym, int group) {
   float ulo = INFINITY, uhi = -INFINITY;
   for (int k = 0; k < K; k++) {
     for (int b = 1; b <= nb; b++) {
-      // bracket: around the threshold of exact arithmetic, (b - q0 - qmax/2 - 1/2) / alpha
-      // (symmetric: (b - Q - 1/2) / alpha), widened until it holds
-      const double center = sym ? (b - qmax - 0.5) / (double)p.alpha[k]
-                                : (b - 0.5 * qmax - 0.5) / (double)p.alpha[k];
-      uint32_t lo = f32_order_key(-INFINITY), hi = f32_order_key(INFINITY);
-      for (double half = 1e-6; half < 4.0; half *= 16.0) {
-        const uint32_t a = f32_order_key((float)(center - half)), z = f32_order_key((float)(center + half));
-        if (int_code(f32_from_order_key(a), p.alpha[k], qmax, sym) < q0 + b &&
-            int_code(f32_from_order_key(z), p.alpha[k], qmax, sym) >= q0 + b) {
-          lo = a;
-          hi = z;
-          break;
-        }
-      }
-      while (hi - lo > 1) {
-        const uint32_t mid = lo + (hi - lo) / 2;
-        if (int_code(f32_from_order_key(mid), p.alpha[k], qmax, sym) >= q0 + b)
-          hi = mid;
-        else
-          lo = mid;
-      }
-      t[n++] = f32_from_order_key(hi);
+      t[n++] = code_threshold(p.alpha[k], sym ? 0.0f : 0.5f * (float)qmax, q0 + b);
       if (b == tie) {
         ulo = fminf(ulo, t[n - 1]);
         uhi = fmaxf(uhi, t[n - 1]);

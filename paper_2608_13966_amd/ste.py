@@ -70,15 +70,20 @@ class QuasarLinear(torch.nn.Module):
     def step(self):
         """One fused AdamW step on the latent weights from their gradient,
         then the reconstruction of the result into ``r`` (in place)."""
-        g = self.weight.grad
+        weight = self.weight
+        g = weight.grad
         if g is None:
             raise RuntimeError("no gradient: call backward() first")
-        self.t += 1
-        if self._out is None:
-            d = Q.Descriptor(*self.weight.shape, w_dtype=Q.F32, g_dtype=Q.F32, **self.cfg)
-            self._out = Q.alloc_outputs(d, self.weight.data, want_r=False, want_diag=True, has_amax=True)
-            self._out["r"] = self.r
-        Q.adamw_reconstruct(self.weight.data, self.m, self.v, g.contiguous(), step=self.t, out=self._out,
-                            r_dtype="bf16", **self.cfg, **self.hp)
-        self.codes, self.scales, self.zeros = self._out["codes"], self._out["scales"], self._out["zeros"]
-        self.weight.grad = None
+        t = self.__dict__["t"] = self.t + 1  # an int: no module registration to look through
+        W = weight.data
+        out = self._out
+        if out is None:
+            d = Q.Descriptor(*W.shape, w_dtype=Q.F32, g_dtype=Q.F32, **self.cfg)
+            out = Q.alloc_outputs(d, W, want_r=False, want_diag=True, has_amax=True)
+            out["r"] = self.r
+            self._out = out
+        Q.adamw_reconstruct(W, self.m, self.v, g.contiguous(), step=t, out=out, r_dtype="bf16", **self.cfg,
+                            **self.hp)
+        if self.codes is not out["codes"] or self.scales is not out["scales"] or self.zeros is not out["zeros"]:
+            self.codes, self.scales, self.zeros = out["codes"], out["scales"], out["zeros"]
+        weight.grad = None
