@@ -241,20 +241,41 @@ __device__ __forceinline__ float max_f32(float a, float b) {
 // All-reduce over aligned runs of L consecutive lanes (L in 1, 2, 4, 8, 16).
 // The patterns pair lanes symmetrically, and IEEE addition / min / max are
 // commutative, so every lane of a run ends with a bit-identical result.
+// x combined with the x of the lane a DPP control names, in one instruction
+// (a separate DPP move feeding the inline min or max would be two).  A DPP
+// operand may not be read within two wait states of its VALU write, which the
+// compiler does not track into inline asm: hence the s_nop.
+#define QUASAR_DPP_MINMAX(NAME, CTRL)                                                                              \
+  __device__ __forceinline__ float NAME##_min(float x) {                                                           \
+    float r;                                                                                                       \
+    asm("s_nop 1\n\tv_min_f32_dpp %0, %1, %1 " CTRL " row_mask:0xf bank_mask:0xf" : "=v"(r) : "v"(x));             \
+    return r;                                                                                                      \
+  }                                                                                                                \
+  __device__ __forceinline__ float NAME##_max(float x) {                                                           \
+    float r;                                                                                                       \
+    asm("s_nop 1\n\tv_max_f32_dpp %0, %1, %1 " CTRL " row_mask:0xf bank_mask:0xf" : "=v"(r) : "v"(x));             \
+    return r;                                                                                                      \
+  }
+QUASAR_DPP_MINMAX(xor1, "quad_perm:[1,0,3,2]")
+QUASAR_DPP_MINMAX(xor2, "quad_perm:[2,3,0,1]")
+QUASAR_DPP_MINMAX(half_mirror, "row_half_mirror")
+QUASAR_DPP_MINMAX(mirror, "row_mirror")
+#undef QUASAR_DPP_MINMAX
+
 template <int L>
 __device__ __forceinline__ float run_min(float x) {
-  if constexpr (L >= 2) x = min_f32(x, dpp_f32<kDppXor1>(x));
-  if constexpr (L >= 4) x = min_f32(x, dpp_f32<kDppXor2>(x));
-  if constexpr (L >= 8) x = min_f32(x, dpp_f32<kDppHalfMirror>(x));
-  if constexpr (L >= 16) x = min_f32(x, dpp_f32<kDppMirror>(x));
+  if constexpr (L >= 2) x = xor1_min(x);
+  if constexpr (L >= 4) x = xor2_min(x);
+  if constexpr (L >= 8) x = half_mirror_min(x);
+  if constexpr (L >= 16) x = mirror_min(x);
   return x;
 }
 template <int L>
 __device__ __forceinline__ float run_max(float x) {
-  if constexpr (L >= 2) x = max_f32(x, dpp_f32<kDppXor1>(x));
-  if constexpr (L >= 4) x = max_f32(x, dpp_f32<kDppXor2>(x));
-  if constexpr (L >= 8) x = max_f32(x, dpp_f32<kDppHalfMirror>(x));
-  if constexpr (L >= 16) x = max_f32(x, dpp_f32<kDppMirror>(x));
+  if constexpr (L >= 2) x = xor1_max(x);
+  if constexpr (L >= 4) x = xor2_max(x);
+  if constexpr (L >= 8) x = half_mirror_max(x);
+  if constexpr (L >= 16) x = mirror_max(x);
   return x;
 }
 template <int L>
@@ -323,14 +344,16 @@ template <int CTRL, int ROW_MASK>
 __device__ __forceinline__ uint32_t dpp_rows(uint32_t id, uint32_t x) {
   return (uint32_t)__builtin_amdgcn_update_dpp((int)id, (int)x, CTRL, ROW_MASK, 0xF, false);
 }
-__device__ __forceinline__ float rows_min(float x) {
-  x = min_f32(x, as_f32(dpp_rows<0x142, 0xA>(as_u32(INFINITY), as_u32(x))));
-  x = min_f32(x, as_f32(dpp_rows<0x143, 0xC>(as_u32(INFINITY), as_u32(x))));
+__device__ __forceinline__ float rows_min(float x) {  // one instruction a step: a row outside the mask keeps its x
+  asm("s_nop 1\n\tv_min_f32_dpp %0, %0, %0 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_min_f32_dpp %0, %0, %0 row_bcast:31 row_mask:0xc bank_mask:0xf"
+      : "+v"(x));
   return as_f32((uint32_t)__builtin_amdgcn_readlane((int)as_u32(x), 63));
 }
 __device__ __forceinline__ float rows_max(float x) {
-  x = max_f32(x, as_f32(dpp_rows<0x142, 0xA>(as_u32(-INFINITY), as_u32(x))));
-  x = max_f32(x, as_f32(dpp_rows<0x143, 0xC>(as_u32(-INFINITY), as_u32(x))));
+  asm("s_nop 1\n\tv_max_f32_dpp %0, %0, %0 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_max_f32_dpp %0, %0, %0 row_bcast:31 row_mask:0xc bank_mask:0xf"
+      : "+v"(x));
   return as_f32((uint32_t)__builtin_amdgcn_readlane((int)as_u32(x), 63));
 }
 template <int CTRL, int ROW_MASK>

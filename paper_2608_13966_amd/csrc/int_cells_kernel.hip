@@ -154,14 +154,19 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
   const int K = p.n_clips;
   const int cmax = p.cells.cmax;
 
+  // Byte offset of cell c's sum of h in its group.  With both sums in a cell,
+  // odd cells hold h w first: the atomics on h then use all LDS banks and not
+  // the even pairs only (and those on h w, 8 bytes to the other side, as well).
+  auto h_offset = [&](int c) { return SPLIT ? (uint32_t)c * 8u : (uint32_t)c * 16u + (uint32_t)(c & 1) * 8u; };
   {  // the tables, read from the kernel-argument segment with per-lane indices
     const IntCells& cl = kernarg_params<IntParams>()->cells;
     if (cmax == 1) {
       const int c0 = cl.base[2 * tid], c1 = cl.base[2 * tid + 1];
-      s_bucket[tid] = make_uint4(as_u32(cl.thr[c0]), (uint32_t)(c0 * CELL), as_u32(cl.thr[c1]), (uint32_t)(c1 * CELL));
+      s_bucket[tid] = make_uint4(as_u32(cl.thr[c0]), h_offset(c0) | h_offset(c0 + 1) << 16, as_u32(cl.thr[c1]),
+                                 h_offset(c1) | h_offset(c1 + 1) << 16);
     } else {
       const int c = cl.base[tid];
-      s_bucket[tid] = make_uint4((uint32_t)(c * CELL), as_u32(cl.thr[c]), as_u32(cl.thr[c + 1]), as_u32(cl.thr[c + 2]));
+      s_bucket[tid] = make_uint4((uint32_t)c, as_u32(cl.thr[c]), as_u32(cl.thr[c + 1]), as_u32(cl.thr[c + 2]));
     }
     s_tp[tid] = (&cl.tp[0][0])[tid];
   }
@@ -262,10 +267,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
 #pragma unroll
       for (int t = 0; t < 4; t++) {
         if constexpr (C == 1) {
-          off[t] = e[t].y + (u[t] >= as_f32(e[t].x) ? CELL : 0u);
+          off[t] = __builtin_amdgcn_ubfe(e[t].y, u[t] >= as_f32(e[t].x) ? 16u : 0u, 16u);
         } else {
-          off[t] = e[t].x + (u[t] >= as_f32(e[t].y) ? CELL : 0u) + (u[t] >= as_f32(e[t].z) ? CELL : 0u);
-          if constexpr (C > 2) off[t] += (u[t] >= as_f32(e[t].w) ? CELL : 0u);
+          uint32_t c = e[t].x + (u[t] >= as_f32(e[t].y) ? 1u : 0u) + (u[t] >= as_f32(e[t].z) ? 1u : 0u);
+          if constexpr (C > 2) c += (u[t] >= as_f32(e[t].w) ? 1u : 0u);
+          off[t] = h_offset((int)c);
         }
         x[t] = w[t];
       }
@@ -277,13 +283,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
         float vi = v[i0 + t];
         asm volatile("" : "+v"(vi));
         const double V = (double)vi;
-        u64* c = cell_at(off[t]);
-        add(c, scaled_to_i64(V, sh));
+        add(cell_at(off[t]), scaled_to_i64(V, sh));
         if constexpr (!SPLIT) {
           const double Wd = (double)x[t];
           const double VW = V * Wd;
           Svww = __builtin_fma(VW, Wd, Svww);
-          add(c + 1, scaled_to_i64(VW, shw));
+          add(cell_at(off[t] ^ 8u), scaled_to_i64(VW, shw));
         }
       }
       if constexpr (SPLIT) {
@@ -306,13 +311,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
   // unless its saliency is 0 (h >= 0, so the cell's sum of h is 0 exactly when
   // every weight in it has h = 0, and those weights add nothing to any moment).
   const int ucell = p.cells.unsafe_cell;
-  const bool group_unsafe = ucell >= 0 && hist[ucell * (CELL / 8)] != 0;
+  const bool group_unsafe = ucell >= 0 && *cell_at(h_offset(ucell)) != 0;
   wave_lds_fence();  // read before the sums are taken in place
 
   // ---- suffix sums over the cells, in place and in integers: the lane's
   // cells are read into registers (a compile-time count, the host rounds cpl
   // up to it; the cells past the last threshold are zero), summed from the
-  // top down, and the total of the members above this one added.
+  // top down, and the total of the members above this one added.  The suffix
+  // sums are written h first in every cell.
   auto suffix = [&](auto cpl_tag) {
     constexpr int C = decltype(cpl_tag)::value;
     if constexpr (SPLIT) {
@@ -329,7 +335,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
       ulonglong2* mc = reinterpret_cast<ulonglong2*>(hist) + j * C;
       ulonglong2 t[C];
 #pragma unroll
-      for (int c = 0; c < C; c++) t[c] = mc[c];
+      for (int c = 0; c < C; c++) {  // C is even, so c's parity is the cell's
+        t[c] = mc[c];
+        if (c & 1) t[c] = make_ulonglong2(t[c].y, t[c].x);
+      }
 #pragma unroll
       for (int c = C - 2; c >= 0; c--) {
         t[c].x += t[c + 1].x;
@@ -477,25 +486,31 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
   // accurately enough (int_fit_ill), or with a weight among merged
   // thresholds, evaluates every clip straight from its weights
   // (int_exact_wave).
+  //
+  // The tests that find such groups cost more per clip than the ranking.  So
+  // the ranking only keeps the least D and |num| of its clips, and one bound
+  // per group over all possible codes (A0 <= Q Sv, A1 <= Q^2 Sv) tells
+  // whether any clip could fail a test; the tests run, clip by clip, only for
+  // the groups it cannot clear (about one in a thousand).
   IntBest best = int_best_init();
   bool full = p.param_dtype != 0;
   bool ill = group_unsafe;
   int bk = -1;
   double bn = 0.0, bd = 1.0, b0 = 0.0, b1 = 0.0, b2 = 0.0;
   if (!full && !group_unsafe) {
+    constexpr double Q = (double)QMAX;
+    double dmin = 1e300, nmin = 1e300;
     // unrolled: the clips' fp64 chains interleave
 #pragma unroll
     for (int t = 0; t < OWN; t++) {
       const int k = j + L * t;
       if (k < K) {
-        ill |= int_fit_ill<SYM, QMAX>(mo, A0[t], A1[t], A2[t]);
-        const double D = SYM ? A1[t] : mo.Sv * A1[t] - A0[t] * A0[t];
-        const double num = SYM ? A2[t] : mo.Sv * A2[t] - A0[t] * mo.Svw;
-        const bool degenerate = SYM ? (A1[t] == 0.0) : (mo.Sv == 0.0 || D <= mo.thr);
+        const double D = SYM ? A1[t] : __builtin_fma(mo.Sv, A1[t], -(A0[t] * A0[t]));
+        const double num = SYM ? A2[t] : __builtin_fma(mo.Sv, A2[t], -(A0[t] * mo.Svw));
+        dmin = min_key(dmin, D);
+        nmin = min_key(nmin, fabs(num));
         const double n2 = num * num;
-        if (degenerate) {
-          full = true;
-        } else if (bk < 0 || n2 * bd > bn * D) {
+        if (t == 0 || n2 * bd > bn * D) {
           bk = k;
           bn = n2;
           bd = D;
@@ -505,10 +520,26 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
         }
       }
     }
+    // int_fit_ill's error bounds at their largest (symmetric: its rel A1 is
+    // far below kFitTol A1, the factor 2 covers it)
+    const double eD = SYM ? 2.0 * mo.qh * Q * Q : __builtin_fma(2.0 * mo.rel * Q * Q, mo.Sv * mo.Sv, mo.eD0);
+    const double eN = SYM ? (mo.qhw + mo.rel * mo.wabs * mo.Sv) * Q : __builtin_fma(mo.eN1 * Q, mo.Sv, mo.eN0);
+    const bool clear = (eD <= kFitTol * dmin) & (eN <= kFitTol * nmin) & (SYM || dmin - eD > mo.thr);
+    if (M::max(clear ? 0.0f : 1.0f) > 0.0f) {
+      bool degenerate = false;
+#pragma unroll
+      for (int t = 0; t < OWN; t++) {
+        if (j + L * t < K) {
+          ill |= int_fit_ill<SYM, QMAX>(mo, A0[t], A1[t], A2[t]);
+          degenerate |= SYM ? (A1[t] == 0.0) : (mo.Sv == 0.0 || mo.Sv * A1[t] - A0[t] * A0[t] <= mo.thr);
+        }
+      }
+      ill = M::max(ill ? 1.0f : 0.0f) > 0.0f;
+      full = M::max(degenerate ? 1.0f : 0.0f) > 0.0f;
+    }
   }
-  ill = M::max(ill ? 1.0f : 0.0f) > 0.0f;
   if (!ill) {
-    if (M::max(full ? 1.0f : 0.0f) > 0.0f) {
+    if (full) {
 #pragma unroll
       for (int t = 0; t < OWN; t++) {
         const int k = j + L * t;

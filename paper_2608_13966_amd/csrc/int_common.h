@@ -573,7 +573,8 @@ __device__ __forceinline__ void int_finish(const IntParams& p, const IntMatrix& 
   // positions u are formed again here from opaque copies of the range: the
   // same expression earlier in the kernel would otherwise be kept, 16 values
   // held in registers through everything in between.
-  float rrho = g.rrho, nc = g.nc;
+  // (constant group: a position whose code is 0 for any clip)
+  float rrho = g.constant ? 0.0f : g.rrho, nc = g.constant ? -0x1p60f : g.nc;
   asm volatile("" : "+v"(rrho), "+v"(nc));
   const bool r_bf16 = W_BF16 || p.r_bf16;
   if (mtx.r) wave_lds_fence();  // the stage's earlier use is done
@@ -589,14 +590,12 @@ __device__ __forceinline__ void int_finish(const IntParams& p, const IntMatrix& 
         const float ui = wr.get(i) * rrho;
         // + 0.0f turns a rounded -0 into +0, so a zero code gives r = s * (+0)
         float q = __builtin_amdgcn_fmed3f(__builtin_rintf(ui * alpha), kQmin, kQmax) + 0.0f;
-        if (g.constant) q = 0.0f;
         qi = (uint32_t)(int)q & ((1u << BITS) - 1u);  // two's complement in BITS bits
         r[t] = a * q;
       } else {
         const float ui = __builtin_fmaf(wr.get(i), rrho, nc);
         float x = __builtin_fmaf(ui, alpha, kBeta);
         float q = __builtin_amdgcn_fmed3f(__builtin_rintf(x), 0.0f, kQmax);
-        if (g.constant) q = 0.0f;
         qi = (uint32_t)q;
         r[t] = __builtin_fmaf(a, q, b);
       }
