@@ -28,8 +28,8 @@
 //
 // The cell sums of h and h w are kept as integers.  Each value is scaled by a
 // power of two fixed per block (from the block's largest h and |w|), to x
-// with |x| < 2^51, and split into hi = rint(x) - 1 and lo = trunc((x -
-// rint(x) + 1) 2^21), in [2^20, 3 2^20]: x = hi + lo 2^-21 whenever x is a
+// with |x| < 2^51, and split into hi = rint(x - 1) and lo = trunc((x - hi)
+// 2^21), in [2^20, 3 2^20]: x = hi + lo 2^-21 whenever x is a
 // multiple of 2^-21, else lo falls short by less than one unit.  Three 64-bit
 // LDS atomics per weight add the high limbs of h and of h w and both low
 // limbs, packed into the halves of one word (the sums of a half over a block
@@ -62,7 +62,7 @@ constexpr int kCells = kRubinThresholds;  // cell ids 0 .. (boundaries) <= 127 <
 constexpr int kHiBits = 51;    // |scaled value| < 2^51: its nearest integer is the high limb
 constexpr int kLoBits = 21;    // the low limb counts units of 2^-21
 constexpr double kMagic = 6755399441055744.0;  // 1.5 * 2^52: x + kMagic rounds x to an integer
-
+constexpr uint32_t kMagicHi = 0x43380000u;     // ... its bit pattern's high word
 
 // E4M3 byte of x (nearest even, |x| clamped to 448 first: the conversion
 // gives NaN above 464), +0 for a zero result.
@@ -74,20 +74,27 @@ __device__ __forceinline__ uint32_t e4m3_byte(float x) {
 __device__ __forceinline__ float e4m3_value(uint32_t e) { return __builtin_amdgcn_cvt_f32_fp8((int)e, 0); }
 
 // x = a s (s a power of two, |x| < 2^51; the product is exact) as hi + lo
-// 2^-21 with hi = rint(x) - 1 and lo = trunc((r + 1) 2^21), r = x - rint(x)
-// in [-1/2, 1/2], so lo lies in [2^20, 3 2^20].  For |y| < 2^51, y + 1.5 2^52
-// lands where the fp64 spacing is 1, so its bit pattern minus that of 1.5
-// 2^52 is rint(y) as a two's-complement integer; r is exact (an fma of the
-// exact product), and (r + 1) 2^21 is rounded once, at a spacing of 2^-31.
-__device__ __forceinline__ void split_limbs(double a, double s, int64_t& hi, uint32_t& lo) {
-  const int64_t mb = __double_as_longlong(kMagic);
-  const double t = __builtin_fma(a, s, kMagic);
-  hi = __double_as_longlong(t) - (mb + 1);
-  const double r = __builtin_fma(a, s, -(t - kMagic));
-  lo = (uint32_t)__builtin_fma(r, 0x1p21, 0x1p21);  // truncates toward zero
+// 2^-21 with hi = rint(x - 1) and lo = trunc((x - hi) 2^21), x - hi in
+// [1/2, 3/2], so lo lies in [2^20, 3 2^20].  t = fma(a, s, 1.5 2^52 - 1) lands
+// where the fp64 spacing is 1: it is 1.5 2^52 + hi, whose bit pattern minus
+// that of 1.5 2^52 (low word zero) is hi as a two's-complement integer.
+// -hi 2^21 is one exact fma of t, and (x - hi) 2^21 one fma more, rounded once
+// at a spacing of 2^-31.  s21 = s 2^21.  The constants sit in registers (an
+// instruction reads one scalar operand, and s is the other).
+struct LimbConsts {
+  double m1, c21, m21;  // 1.5 2^52 - 1, -2^21, 1.5 2^73
+  __device__ __forceinline__ LimbConsts() : m1(kMagic - 1.0), c21(-0x1p21), m21(kMagic * 0x1p21) {
+    asm volatile("" : "+v"(m1), "+v"(c21), "+v"(m21));
+  }
+};
+__device__ __forceinline__ void split_limbs(double a, double s, double s21, const LimbConsts& k, int64_t& hi,
+                                            uint32_t& lo) {
+  const double t = __builtin_fma(a, s, k.m1);
+  const uint64_t b = (uint64_t)__double_as_longlong(t);
+  hi = (int64_t)(((uint64_t)((uint32_t)(b >> 32) - kMagicHi) << 32) | (uint32_t)b);
+  lo = (uint32_t)__builtin_fma(a, s21, __builtin_fma(t, k.c21, k.m21));  // truncates toward zero
 }
 static_assert(kLoBits == 21, "split_limbs scales the remainder by 2^21");
-constexpr uint32_t kLoZero = 1u << kLoBits;  // the low limb of every x below 2^-21: hi + lo 2^-21 = 0
 // the sum of n values from the sums of their high and low limbs (the high
 // sums stay below 2^60 in magnitude)
 __device__ __forceinline__ double join_limbs(int64_t hi, uint32_t lo) {
@@ -126,8 +133,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5))) v
   __shared__ float s_thr[BK ? 1 : kCells];        // tree form: thresholds in search-tree order
   __shared__ uint4 s_bucket[BK ? kCellBuckets : 1];  // bucket form: first cell, next three thresholds
   __shared__ uint8_t s_tpos[kMaxClips][9];        // cell range of code b under clip k
-  __shared__ float s_lut[kWaves][8];
-  __shared__ uint32_t s_lutb[kWaves][8];
+  __shared__ __align__(8) uint8_t s_lut[kWaves][8];  // the winner's codebook, E4M3 bytes
   __shared__ float s_alpha[kMaxClips], s_clip[kMaxClips];
 
   const int tid = threadIdx.x;
@@ -251,14 +257,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5))) v
   }
   const float c = 0.5f * (mx + mn);
   const float rho = 0.5f * (mx - mn);
-  const float rrho = 1.0f / rho;
-  const float nc = -(c * rrho);
+  // a constant block's positions give code 0 under any clip
+  const float rrho = constant ? 0.0f : 1.0f / rho;
+  const float nc = constant ? -0x1p60f : -(c * rrho);
   float u[NE];
 #pragma unroll
   for (int i = 0; i < NE; i++) u[i] = __builtin_fmaf(w[i], rrho, nc);
 
-  float* lutf = s_lut[wave];
-  uint32_t* lutb = s_lutb[wave];
+  uint8_t* const lut = s_lut[wave];
   double best_key = __longlong_as_double(0x7ff0000000000000ll);  // +inf
 
   if (!constant) {  // uniform
@@ -282,7 +288,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5))) v
       // the bucket's first cell plus cmax compares (thresholds outside u's
       // bucket lie on the far side of u; the padding is NaN), four bucket
       // reads in flight at a time
-      const float ulo = p.unsafe_lo, uhi = p.unsafe_hi;
       auto bin = [&](auto cmax_tag) {
         constexpr int C = decltype(cmax_tag)::value;
 #pragma unroll
@@ -297,7 +302,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5))) v
             if constexpr (C > 1) c += (x >= as_f32(e[t].z) ? 1 : 0);
             if constexpr (C > 2) c += (x >= as_f32(e[t].w) ? 1 : 0);
             pos[i0 + t] = c;
-            unsafe |= (x >= ulo) & (x <= uhi);
           }
         }
       };
@@ -307,6 +311,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5))) v
         bin(std::integral_constant<int, 2>{});
       else
         bin(std::integral_constant<int, 3>{});
+      // a weight in [unsafe_lo, unsafe_hi] (both negative floats, whose bit
+      // patterns grow downwards; both +inf: none): the least of the
+      // differences, as unsigned integers, is at most the span's
+      const uint32_t top = as_u32(p.unsafe_hi);
+      uint32_t near = 0xffffffffu;
+#pragma unroll
+      for (int i = 0; i < NE; i++) near = min(near, as_u32(u[i]) - top);
+      unsafe = near <= as_u32(p.unsafe_lo) - top;
     } else {
       // descend the implicit search tree (node n has children 2n, 2n + 1; the
       // leaves 128 .. 255 are the counts), one level for all 8 weights at a
@@ -326,22 +338,29 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5))) v
     // are summed directly below
     const bool block_unsafe = __ballot(unsafe) != 0;  // uniform
     const double s_h = __builtin_ldexp(1.0, sh_exp), s_hw = __builtin_ldexp(1.0, sw_exp);
-    bool lost = false;
+    const double s_h21 = __builtin_ldexp(1.0, sh_exp + kLoBits), s_hw21 = __builtin_ldexp(1.0, sw_exp + kLoBits);
+    const LimbConsts lc;
 #pragma unroll
     for (int i = 0; i < NE; i++) {
       int64_t xh, xw;
       uint32_t lh, lw;
-      split_limbs(H[i], s_h, xh, lh);
-      split_limbs(HW[i], s_hw, xw, lw);
+      split_limbs(H[i], s_h, s_h21, lc, xh, lh);
+      split_limbs(HW[i], s_hw, s_hw21, lc, xw, lw);
       atomicAdd(reinterpret_cast<unsigned long long*>(&limb[0][pos[i]]), (unsigned long long)xh);
       atomicAdd(reinterpret_cast<unsigned long long*>(&limb[1][pos[i]]), (unsigned long long)xw);
       atomicAdd(reinterpret_cast<unsigned long long*>(&limb[2][pos[i]]), ((unsigned long long)lw << 32) | lh);
-      if (v[i] > 0.0f && xh == -1 && lh == kLoZero) {  // rare: h below the fixed point
-        limb[3][pos[i]] = 1;
-        lost = true;
-      }
     }
-    const bool block_lost = __ballot(lost) != 0;  // uniform
+    // a saliency in (0, 2^-21 units) is 0 in the limbs (rare): its cell is flagged
+    const uint32_t lim = as_u32(__builtin_ldexpf(1.0f, -kLoBits - sh_exp));
+    uint32_t least = 0xffffffffu;  // the least h > 0, as its bit pattern minus 1 (h = 0 wraps to the largest)
+#pragma unroll
+    for (int i = 0; i < NE; i++) least = min(least, as_u32(v[i]) - 1u);
+    const bool block_lost = __ballot(lim != 0u && least < lim - 1u) != 0;  // uniform
+    if (block_lost) {
+#pragma unroll
+      for (int i = 0; i < NE; i++)
+        if (as_u32(v[i]) - 1u < lim - 1u) limb[3][pos[i]] = 1;
+    }
     wave_lds_fence();
 
     // ---- exclusive prefix sums over the cells: lane 16 j + c takes cells
@@ -373,7 +392,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5))) v
     wave_lds_fence();
 
     // ---- clips, 8 at a time: lane (kk, b) owns codebook entry b of clip k0+kk --
+    // the lane keeps the better of its clips, and the clips meet once at the end
     const int kk = lane >> 3, b = lane & 7;
+    uint32_t best_e = 0;
     for (int k0 = 0; k0 < K; k0 += 8) {
       const int k = k0 + kk;
       const bool live = k < K;
@@ -422,48 +443,58 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5))) v
         meanf = __builtin_fmaf((float)b, (2.0f * fr) / 7.0f, c - fr);
       }
       const uint32_t e = e4m3_byte(meanf);
-      const float cvf = e4m3_value(e);
-      const double cv = (double)cvf;
+      const double cv = (double)e4m3_value(e);
       // score: sum_b (C_b^2 H_b - 2 C_b HW_b) + sum h w^2, over the 8 lanes of the clip
       const double score = sww + run_sum<8>(cv * (cv * hb - 2.0 * hwb));
-      double key = live ? make_key(score, k) : __longlong_as_double(0x7ff0000000000000ll);
-      // the 8 lanes of a clip hold one key (bit-identical sums): the two
-      // clips of a row meet with one mirror step, then the rows combine
-      const double kmin = rows_min_f64(min_key(key, dpp_f64<kDppMirror>(key)));
-      if (kmin < best_key) {  // uniform
-        best_key = kmin;
-        if (k == key_index(kmin)) {  // the 8 lanes of the winning clip
-          lutf[b] = cvf;
-          lutb[b] = e;
-        }
+      const double key = live ? make_key(score, k) : __longlong_as_double(0x7ff0000000000000ll);
+      if (key < best_key) {
+        best_key = key;
+        best_e = e;
       }
     }
+    // the 8 lanes of a clip hold one key (bit-identical sums): the two clips
+    // of a row meet with one mirror step, then the rows combine
+    const double kmin = rows_min_f64(min_key(best_key, dpp_f64<kDppMirror>(best_key)));
+    if (best_key == kmin) lut[b] = (uint8_t)best_e;  // the 8 lanes of the winning clip
+    best_key = kmin;
   } else if (lane < 8) {  // constant block: every code 0, every entry E4M3(w)
-    const uint32_t e = e4m3_byte(mn);
-    lutf[lane] = e4m3_value(e);
-    lutb[lane] = e;
+    lut[lane] = (uint8_t)e4m3_byte(mn);
   }
   wave_lds_fence();
 
   // ---- emit ------------------------------------------------------------------
+  const uint2 book = *reinterpret_cast<const uint2*>(lut);
   const int kstar = constant ? 0 : key_index(best_key);
   float err;
   if (constant) {
-    const double d = (double)lutf[0] - (double)mn;
+    const double d = (double)e4m3_value(book.x & 0xffu) - (double)mn;
     err = (float)(sh * d * d);
   } else {
     err = (float)__longlong_as_double(__double_as_longlong(best_key) & ~15ll);
   }
+  // the codes as bytes (v_cvt_pk_u8_f32 rounds to nearest even and takes
+  // negative values to 0); a byte permute of the codebook by four codes gives
+  // their four entries
   const float alpha = s_alpha[kstar];
-  uint32_t bits = 0;
+  uint32_t q4[2] = {0u, 0u};
+#pragma unroll
+  for (int i = 0; i < NE; i++)
+    q4[i >> 2] = __builtin_amdgcn_cvt_pk_u8_f32(fminf(__builtin_fmaf(u[i], alpha, 3.5f), 7.0f), i & 3, q4[i >> 2]);
   float r[NE];
 #pragma unroll
-  for (int i = 0; i < NE; i++) {
-    const float x = __builtin_fmaf(u[i], alpha, 3.5f);
-    uint32_t q = (uint32_t)__builtin_amdgcn_fmed3f(__builtin_rintf(x), 0.0f, 7.0f);
-    if (constant) q = 0;
-    bits |= q << (3 * i);
-    r[i] = lutf[q];
+  for (int t = 0; t < 2; t++) {
+    const int e = (int)__builtin_amdgcn_perm(book.y, book.x, q4[t]);
+    const auto r01 = __builtin_amdgcn_cvt_pk_f32_fp8(e, false), r23 = __builtin_amdgcn_cvt_pk_f32_fp8(e, true);
+    r[4 * t] = r01[0]; r[4 * t + 1] = r01[1];
+    r[4 * t + 2] = r23[0]; r[4 * t + 3] = r23[1];
+  }
+  // 3-bit stream: a dot product with 1, 8, 64 packs three codes, the fourth
+  // byte joins at bit 9
+  uint32_t bits = 0;
+#pragma unroll
+  for (int t = 0; t < 2; t++) {
+    const uint32_t b12 = __builtin_amdgcn_udot4(q4[t], 0x00400801u, 0u, false) | ((q4[t] >> 24) << 9);
+    bits |= b12 << (12 * t);
   }
   // 24 bits per lane at byte offset 3 lane of the block's 192-byte stream:
   // lanes 4i .. 4i + 3 hold its dwords 3i .. 3i + 2, which lanes 4i, 4i + 1 and
@@ -488,8 +519,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5))) v
       st128(rp + 4, make_uint4(as_u32(r[4]), as_u32(r[5]), as_u32(r[6]), as_u32(r[7])));
     }
   }
-  if (lane < 8) mtx.lut[bid * 8 + lane] = (uint8_t)lutb[lane];
   if (lane == 0) {
+    *reinterpret_cast<uint2*>(mtx.lut + bid * 8) = book;
     if (mtx.best_clip) mtx.best_clip[bid] = (uint8_t)kstar;
     if (mtx.err) mtx.err[bid] = err;
   }
