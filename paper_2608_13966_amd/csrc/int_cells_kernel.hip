@@ -37,11 +37,13 @@
 // the VALU and the LDS each busy two thirds of the time.  Measured steps, all
 // on that set: fp64 suffix sums, rounded cell by cell in two passes over the
 // LDS, and binning and atomics as two loops: 688 us; in integers, one pass in
-// registers, one loop: 638; one compare per weight: 632-642.
+// registers, one loop, one compare per weight: 643; the fit's tests once per
+// group instead of once per clip: 635; h and h w swapped in odd cells: 634
+// (Qwen3-0.6B set, INT3 with 8 clips: 48.9, 42.0, 41.8, 41.2).
 // Forms.  Both sums in a cell (16 bytes) keep four workgroups on a compute
 // unit up to 10 cells a lane.  Beyond that the cells' LDS would leave two: the
 // SPLIT form takes h and then h w through 8-byte cells (each weight's cell is
-// kept, one byte).  INT3 g128 with 15 clips (93 cells), the Llama set: 727 us;
+// kept, one byte).  INT3 g128 with 15 clips (93 cells), the Llama set: 716 us;
 // both sums at once 1018; the direct kernel 1172.  A form with 8 weights per
 // lane (half the groups per wavefront, so half the LDS) took 750 us there,
 // and 59 against 45 us on the Qwen3-0.6B set (INT3, 8 clips): its per-group

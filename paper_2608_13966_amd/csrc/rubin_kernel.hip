@@ -48,6 +48,14 @@
 // block and its 8 consecutive columns 8 (l % 8) .. 8 (l % 8) + 7.  The
 // per-clip phase runs 8 clips at a time, lane (k, b) = (l / 8, l % 8) owning
 // codebook entry b of clip k.
+//
+// What bounds it: on the Llama-3.1-8B layer set (15 clips, EMA, 14.4 bytes per
+// weight) 727 us, 4.3 TB/s, with the LDS busy three quarters of the time (24
+// atomics per wavefront at random cells, 16 cycles each: 400 of its 800
+// cycles) and the VALU about as much.  754 us before the limbs were split with
+// three fmas (six instructions before), the argmin taken once over all clips,
+// the tie and lost-saliency tests made by one unsigned minimum each, and the
+// codes emitted as bytes that permute the codebook (no LDS lookup per weight).
 #include <type_traits>
 
 #include "device_common.h"
