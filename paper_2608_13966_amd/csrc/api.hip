@@ -641,10 +641,15 @@ int launch_path(const quasar_desc* d, const void* W, void* Wu, float* m, float* 
     if (tensor_amax != nullptr) {
       p.amax = tensor_amax;
     } else {
-      unsigned* ws = static_cast<unsigned*>(workspace);
-      e = quasar::launch_absmax(W, w_bf16, d->rows * d->cols, ws, st);
+      const int64_t n_chunks = d->rows * d->cols / (w_bf16 ? 8 : 4);
+      if (n_chunks <= quasar::kAbsPartialChunks) {
+        p.n_partial = (int)std::min<int64_t>(quasar::kAbsPartials, (n_chunks + 1023) / 1024);
+        e = quasar::launch_absmax_partial(W, w_bf16, n_chunks, p.n_partial, static_cast<float*>(workspace), st);
+      } else {
+        e = quasar::launch_absmax(W, w_bf16, d->rows * d->cols, static_cast<unsigned*>(workspace), st);
+      }
       if (e != hipSuccess) return QUASAR_ERR_DEVICE;
-      p.amax = reinterpret_cast<const float*>(ws);
+      p.amax = static_cast<const float*>(workspace);
     }
     e = quasar::launch_nvfp4(p, w_bf16, ema_mode, st);
   }

@@ -136,7 +136,13 @@ void nvfp4_reconstruct_kernel(Nvfp4Params p) {
     for (int i = 0; i < N; i++) v[i] = weight_of(v[i], p.weighting);
   }
 
-  const float amax = __builtin_nontemporal_load(mtx.amax);
+  float amax;
+  if (p.n_partial > 0) {  // the partial maxima of absmax_partial_kernel, at most one per lane
+    const int lane = tid & 63;
+    amax = rows_max(run_max<16>(mtx.amax[lane < p.n_partial ? lane : 0]));
+  } else {
+    amax = __builtin_nontemporal_load(mtx.amax);
+  }
   const float st = amax / 2688.0f;  // 6 * 448
   float m = 0.0f;
 #pragma unroll
@@ -401,6 +407,38 @@ __global__ __launch_bounds__(kThreads) void absmax_kernel(AbsmaxTable t) {
   }
 }
 
+// The absmax of one matrix as at most kAbsPartials maxima, out[b] of its b-th
+// stretch: plain stores, so nothing has to be cleared first, and the
+// reconstruct kernel combines them (a wavefront holds one per lane).
+template <bool W_BF16>
+__global__ __launch_bounds__(kAbsPartialThreads) void absmax_partial_kernel(const uint4* src, int64_t n_chunks,
+                                                                            float* out) {
+  __shared__ float s_m[kAbsPartialThreads / 64];
+  const int64_t per = (n_chunks + gridDim.x - 1) / gridDim.x;
+  const int64_t c0 = blockIdx.x * per;
+  const int64_t c1 = min(c0 + per, n_chunks);
+  constexpr int kLoads = 4;  // in flight
+  float m = 0.0f;
+#pragma unroll 1
+  for (int64_t c = c0 + threadIdx.x; c < c1; c += kLoads * kAbsPartialThreads) {
+    uint4 buf[kLoads];
+#pragma unroll
+    for (int u = 0; u < kLoads; u++) {
+      const int64_t cu = c + u * kAbsPartialThreads;
+      buf[u] = cu < c1 ? src[cu] : make_uint4(0u, 0u, 0u, 0u);
+    }
+#pragma unroll
+    for (int u = 0; u < kLoads; u++) m = fmaxf(m, chunk_absmax<W_BF16>(buf[u]));
+  }
+  m = rows_max(run_max<16>(m));
+  if ((threadIdx.x & 63) == 0) s_m[threadIdx.x >> 6] = m;
+  __syncthreads();
+  if (threadIdx.x < 64) {  // one wavefront combines the workgroup's
+    m = rows_max(run_max<16>(threadIdx.x < kAbsPartialThreads / 64 ? s_m[threadIdx.x] : 0.0f));
+    if (threadIdx.x == 0) out[blockIdx.x] = m;
+  }
+}
+
 template <bool W_BF16, int EMA>
 hipError_t launch_kc(const Nvfp4Params& p, hipStream_t s) {
   const int64_t blocks = p.batch.n > 1 ? p.batch.total_blocks : (p.n_blocks + kThreads - 1) / kThreads;
@@ -451,6 +489,17 @@ hipError_t launch_absmax(const AbsmaxTable& t, bool w_bf16, hipStream_t s) {
     hipLaunchKernelGGL(absmax_kernel<true>, grid, block, 0, s, t);
   else
     hipLaunchKernelGGL(absmax_kernel<false>, grid, block, 0, s, t);
+  return hipGetLastError();
+}
+
+hipError_t launch_absmax_partial(const void* W, bool w_bf16, int64_t n_chunks, int n_partial, float* out,
+                                 hipStream_t s) {
+  const dim3 grid((unsigned)n_partial), block(kAbsPartialThreads);
+  const uint4* src = static_cast<const uint4*>(W);
+  if (w_bf16)
+    hipLaunchKernelGGL(absmax_partial_kernel<true>, grid, block, 0, s, src, n_chunks, out);
+  else
+    hipLaunchKernelGGL(absmax_partial_kernel<false>, grid, block, 0, s, src, n_chunks, out);
   return hipGetLastError();
 }
 

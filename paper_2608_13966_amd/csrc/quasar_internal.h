@@ -163,6 +163,7 @@ struct Nvfp4Params {
   float* err;
   float* tensor_scale;  // [1] output S_t
   const float* amax;    // [1] tensor absmax (caller's, or the workspace filled by the amax pass)
+  int n_partial;        // > 0: amax holds that many partial maxima (single-matrix workspace path)
   int64_t n_blocks;
   float beta2, omb2;
   int n_clips;
@@ -250,6 +251,18 @@ constexpr int64_t absmax_blocks(int64_t n_chunks) {
   return (n_chunks + (int64_t)kThreads * kAbsSpan - 1) / ((int64_t)kThreads * kAbsSpan);
 }
 hipError_t launch_absmax(const AbsmaxTable& t, bool w_bf16, hipStream_t s);
+// The workspace path of one matrix: n_partial maxima into the workspace, one
+// per workgroup (no clearing), which the reconstruct kernel combines.  At most
+// one per lane of a wavefront, and what the 256-byte workspace holds.
+constexpr int kAbsPartials = 64;
+constexpr int kAbsPartialThreads = 1024;
+// Up to 16 MB of W: 64 workgroups read it in about the time a clearing launch
+// takes (us per call, against clearing and one atomic per workgroup: 0.3 MB
+// 7.5 / 9.8, 4 MB 12.7 / 15.1, 17 MB 29.0 / 31.1; 34 MB 51.7 / 50.5, 67 MB
+// 75 / 63, where the whole chip reads faster than a quarter of it).
+constexpr int64_t kAbsPartialChunks = 1 << 20;
+hipError_t launch_absmax_partial(const void* W, bool w_bf16, int64_t n_chunks, int n_partial, float* out,
+                                 hipStream_t s);
 // amax over n elements of W into *ws (as fp32 bits); clears *ws first.
 hipError_t launch_absmax(const void* W, bool w_bf16, int64_t n, unsigned* ws, hipStream_t s);
 
