@@ -31,8 +31,20 @@ constexpr int N = kIntN;  // weights per lane
 // SYM: symmetric groups (r = s q, q in [-Q, Q], Q = 2^(BITS-1) - 1, range
 // [-f m, f m] with m = max |w|, scale-only fit); otherwise asymmetric groups
 // (r = s q + z, q in [0, 2^BITS - 1], range [c - f rho, c + f rho]).
+//
+// Wavefronts per SIMD: symmetric groups have two moments a clip and their
+// saliencies are dead after the pass (the exact path reads them again), so 8
+// clips fit the 96 VGPRs of five and 12 the 128 of four; fp32 W is held in 8
+// more, and 2 of them spill.  Asymmetric groups at five spill 34 and lose
+// (Llama set, INT4 g128, 8 clips: symmetric 663 -> 643 us, asymmetric 728 -> 924).
+// At four, the saliencies' registers are worth 1 us to a launch that leaves one
+// wavefront per SIMD (INT3 g64 on 3.6 M weights: 20.5 -> 19.7 us).
+constexpr int int_direct_waves(int KC, bool multi, bool sym) {
+  if (sym) return KC > 8 || multi ? 4 : 5;
+  return KC > 8 || multi ? 3 : 4;
+}
 template <bool W_BF16, int EMA, int BITS, int G, int KC, bool MULTI, bool SYM>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu((KC > 8 || MULTI) ? 3 : 4)))
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(int_direct_waves(KC, MULTI, SYM))))
 void int_reconstruct_kernel(IntParams p) {
   constexpr int L = G / N;          // lanes per group
   constexpr int GPW = 64 / L;       // groups per wavefront
@@ -183,9 +195,18 @@ void int_reconstruct_kernel(IntParams p) {
   // a group whose fit the moments cannot fix accurately enough: every clip
   // again, straight from the weights
   {
+    // the saliencies again, so that their registers are free in between: v'
+    // when this kernel stored it, written by another lane of this wavefront,
+    // which the workgroup-scope fences make visible
     auto load_h = [&](float (&hv)[N]) {
+      if constexpr (EMA != 0) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+      }
+      load16<false>(mtx.v, e0, hv);
 #pragma unroll
-      for (int i = 0; i < N; i++) hv[i] = v[i];
+      for (int i = 0; i < N; i++) hv[i] = weight_of(hv[i], p.weighting);
     };
     const bool ill = run_max<L>(best.ill ? 1.0f : 0.0f) > 0.0f;
     int_exact_wave<L, SYM, QMAX, false, W_BF16>(p, wr, load_h, rg, s_alpha, s_clip, lane,

@@ -58,3 +58,29 @@ def test_binned_forms(fmt, bits, group, clips, w_bf16, ema, rows):
     Wt = torch.from_numpy(W).cuda()
     v = torch.from_numpy(np.exp(rng.standard_normal(W.shape) * 3).astype(np.float32)).cuda()
     run_case(name + ".thresholds", *W.shape, 0, fmt=fmt, bits=bits, group=group, clips=clips, w_bf16=False, W=Wt, v=v)
+
+
+@pytest.mark.parametrize("fmt,bits,group,k", [("int", 2, 64, 12), ("int", 3, 128, 15), ("int", 4, 128, 8),
+                                              ("int_sym", 4, 128, 8), ("int_sym", 4, 64, 12), ("int_sym", 4, 128, 16)])
+@pytest.mark.parametrize("w_bf16", [True, False])
+def test_exact_path_sees_updated_saliency(fmt, bits, group, k, w_bf16):
+    """Groups whose moments cannot fix the fit are evaluated from saliencies
+    that the kernel reads again after the fused EMA stored them.  The gradient
+    puts nearly all of v' on one weight and v on another, so the saliencies
+    before the update give another fit."""
+    rows, cols = 5, 3 * group
+    rng = np.random.default_rng(k + group)
+    W = (rng.standard_normal((rows, cols)) * 0.02).astype(np.float32)
+    v = rng.random((rows, cols)).astype(np.float32) / group
+    g = np.zeros((rows, cols), dtype=np.float32)
+    for i in range(rows * cols // group):
+        seg = slice(i * group, (i + 1) * group)
+        at = i * group + rng.integers(1, group)
+        v.flat[at - 1] = 1.0
+        v.flat[seg] *= np.float32(10.0 ** -(6 + i % 4))
+        g.flat[at] = 32.0
+    Wt = torch.from_numpy(W).cuda()
+    run_case(f"exact.ema.{fmt}{bits}.g{group}.K{k}.{w_bf16}", rows, cols, 0, fmt=fmt, bits=bits, group=group,
+             clips=tuple(synth.clip_grid(1.0, 0.6, k)), w_bf16=w_bf16, ema=True,
+             W=Wt.bfloat16() if w_bf16 else Wt, v=torch.from_numpy(v).cuda(), g=torch.from_numpy(g).cuda().bfloat16(),
+             near_limit=rows * cols // group)
