@@ -86,6 +86,16 @@ __device__ __forceinline__ double div_f64(double n, double d, double rd) {
 __device__ __forceinline__ uint4 ld128(const void* p) { return *reinterpret_cast<const uint4*>(p); }
 __device__ __forceinline__ void st128(void* p, uint4 v) { *reinterpret_cast<uint4*>(p) = v; }
 
+// ... non-temporal: for lines that one instruction of the wavefront reads or
+// writes whole (pieces of a line meet in the caches, which these pass by)
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ uint4 ld128_nt(const void* p) {
+  return __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p)));
+}
+__device__ __forceinline__ void st128_nt(void* p, uint4 v) {
+  __builtin_nontemporal_store(__builtin_bit_cast(u32x4, v), reinterpret_cast<u32x4*>(p));
+}
+
 // Load N = 16 consecutive elements of a fp32 or bf16 tensor as fp32.
 template <bool BF16>
 __device__ __forceinline__ void load16(const void* base, int64_t e0, float (&x)[16]) {
@@ -441,7 +451,6 @@ __device__ __forceinline__ void wave_put(const WaveImage& im, int c, uint4 x) {
   const int ch = im.idx * ESZ + c;
   im.stage[ch + ch / PER] = x;
 }
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 template <int ESZ, int PER>
 __device__ __forceinline__ void wave_flush(const WaveImage& im, void* base) {
   static_assert(ESZ == 2 || ESZ == 4, "bf16 or fp32 elements");
@@ -453,8 +462,7 @@ __device__ __forceinline__ void wave_flush(const WaveImage& im, void* base) {
   for (int t = 0; t < ESZ; t++) {
     const int ch = im.lane + 64 * t;
     const uint4 x = im.stage[ch + ch / PER];
-    if ((int64_t)ch * (16 / ESZ) < im.n)
-      __builtin_nontemporal_store(__builtin_bit_cast(u32x4, x), reinterpret_cast<u32x4*>(out + ch));
+    if ((int64_t)ch * (16 / ESZ) < im.n) st128_nt(out + ch, x);
   }
   wave_lds_fence();
 }

@@ -50,12 +50,13 @@
 // codebook entry b of clip k.
 //
 // What bounds it: on the Llama-3.1-8B layer set (15 clips, EMA, 14.4 bytes per
-// weight) 727 us, 4.3 TB/s, with the LDS busy three quarters of the time (24
+// weight) 711 us, 4.4 TB/s, with the LDS busy three quarters of the time (24
 // atomics per wavefront at random cells, 16 cycles each: 400 of its 800
 // cycles) and the VALU about as much.  754 us before the limbs were split with
 // three fmas (six instructions before), the argmin taken once over all clips,
 // the tie and lost-saliency tests made by one unsigned minimum each, and the
-// codes emitted as bytes that permute the codebook (no LDS lookup per weight).
+// codes emitted as bytes that permute the codebook (no LDS lookup per weight),
+// 718 before whole lines were loaded and stored non-temporally.
 #include <type_traits>
 
 #include "device_common.h"
@@ -187,8 +188,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5))) v
 
   // ---- load (each byte once), optional fused EMA, weighting ------------------
   float w[NE], v[NE];
+  // bf16 W and g, and a bf16 r: 8 lanes' 16 bytes are one row of the block, a
+  // whole line, so they pass by the caches (Llama set: 718 -> 711 us)
   if constexpr (W_BF16) {
-    const uint4 t = ld128(reinterpret_cast<const uint16_t*>(mtx.W) + e0);
+    const uint4 t = ld128_nt(reinterpret_cast<const uint16_t*>(mtx.W) + e0);
     const uint32_t d[4] = {t.x, t.y, t.z, t.w};
 #pragma unroll
     for (int k = 0; k < 4; k++) {
@@ -209,7 +212,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5))) v
   if constexpr (EMA != 0) {
     float g[NE];
     if constexpr (EMA == 1) {
-      const uint4 t = ld128(reinterpret_cast<const uint16_t*>(mtx.g) + e0);
+      const uint4 t = ld128_nt(reinterpret_cast<const uint16_t*>(mtx.g) + e0);
       const uint32_t d[4] = {t.x, t.y, t.z, t.w};
 #pragma unroll
       for (int k = 0; k < 4; k++) {
@@ -518,7 +521,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5))) v
   }
   if (mtx.r) {
     if constexpr (W_BF16) {
-      st128(reinterpret_cast<uint16_t*>(mtx.r) + e0,
+      st128_nt(reinterpret_cast<uint16_t*>(mtx.r) + e0,
             make_uint4(pack_bf16x2(r[0], r[1]), pack_bf16x2(r[2], r[3]), pack_bf16x2(r[4], r[5]),
                        pack_bf16x2(r[6], r[7])));
     } else {
