@@ -373,9 +373,16 @@ __device__ __forceinline__ float chunk_absmax(uint4 t) {
 // loads chunks t, t + 256, ... (each load instruction reads 1 KB contiguous per
 // wavefront), kAbsBatch loads in flight at a time; then a DPP / LDS maximum
 // and at most one atomicMax on the fp32 bit pattern per workgroup.
+constexpr int64_t kLastLevelCache = 256ll << 20;  // bytes
 constexpr int64_t kAbsChunks = (int64_t)kThreads * kAbsSpan;
 
-template <bool W_BF16>
+//
+// NT: non-temporal loads, for matrices larger than the last-level cache: what
+// this pass would leave there is gone when the reconstruction reads W (Llama
+// set with its reconstruction, 436 MB of W: 590 -> 565 us).  Smaller sets are
+// read from that cache again (16 to 100 MB: 1 to 3% slower with them, 235 MB
+// the same).
+template <bool W_BF16, bool NT>
 __global__ __launch_bounds__(kThreads) void absmax_kernel(AbsmaxTable t) {
   __shared__ float s_m[kThreads / 64];
   // the table is read from the kernel-argument segment (see batch_slot)
@@ -400,7 +407,7 @@ __global__ __launch_bounds__(kThreads) void absmax_kernel(AbsmaxTable t) {
 #pragma unroll
     for (int u = 0; u < kAbsBatch; u++) {
       const int64_t c = c0 + (int64_t)(b0 + u) * kThreads;
-      buf[u] = c < n_chunks ? src[c] : make_uint4(0u, 0u, 0u, 0u);
+      buf[u] = c < n_chunks ? (NT ? ld128_nt(src + c) : src[c]) : make_uint4(0u, 0u, 0u, 0u);
     }
 #pragma unroll
     for (int u = 0; u < kAbsBatch; u++) m = fmaxf(m, chunk_absmax<W_BF16>(buf[u]));
@@ -498,10 +505,17 @@ hipError_t launch_clear_all(const AbsmaxTable& t, hipStream_t s) {
 hipError_t launch_absmax(const AbsmaxTable& t, bool w_bf16, hipStream_t s) {
   hipLaunchKernelGGL(absmax_clear_all_kernel, dim3(1), dim3(64), 0, s, t);
   const dim3 grid((unsigned)t.block0[t.n]), block(kThreads);
-  if (w_bf16)
-    hipLaunchKernelGGL(absmax_kernel<true>, grid, block, 0, s, t);
+  int64_t chunks = 0;
+  for (int i = 0; i < t.n; i++) chunks += t.n_chunks[i];
+  const bool nt = chunks * 16 > kLastLevelCache;
+  if (w_bf16 && nt)
+    hipLaunchKernelGGL((absmax_kernel<true, true>), grid, block, 0, s, t);
+  else if (w_bf16)
+    hipLaunchKernelGGL((absmax_kernel<true, false>), grid, block, 0, s, t);
+  else if (nt)
+    hipLaunchKernelGGL((absmax_kernel<false, true>), grid, block, 0, s, t);
   else
-    hipLaunchKernelGGL(absmax_kernel<false>, grid, block, 0, s, t);
+    hipLaunchKernelGGL((absmax_kernel<false, false>), grid, block, 0, s, t);
   return hipGetLastError();
 }
 

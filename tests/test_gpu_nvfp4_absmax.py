@@ -34,3 +34,19 @@ def test_workspace_absmax_matches_supplied(rows, cols, w_bf16, where):
     assert float(a["tensor_scale"][0]) == float(b["tensor_scale"][0])
     for k in ("codes", "scales", "r", "best_clip", "err"):
         assert torch.equal(a[k], b[k]), k
+
+
+@pytest.mark.parametrize("rows", [8192, 8193])  # 256 MiB of bf16 W, the last with cached loads, and the next
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_absmax_around_the_last_level_cache(rows, dtype):
+    cols = 16384 if dtype == torch.bfloat16 else 8192
+    W = torch.zeros(rows, cols, dtype=dtype, device="cuda")
+    a = torch.full((4,), 7.0, device="cuda")
+    for at in (0, W.numel() // 2 + 1, W.numel() - 1):
+        W.view(-1)[at] = -3.0
+        s = Q.quasar_absmax(Q.Descriptor(rows, cols, fmt="nvfp4", bits=4, group=16, clips=(1.0,),
+                                         w_dtype=Q.BF16 if dtype == torch.bfloat16 else Q.F32),
+                            W, a, torch.cuda.current_stream().cuda_stream)
+        assert s == Q.OK
+        assert float(a[0]) == 3.0
+        W.view(-1)[at] = 0.0
