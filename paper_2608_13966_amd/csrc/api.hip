@@ -423,10 +423,10 @@ int int_cells_per_lane(int n_cells, int group, bool split) {
 // form.  Up to 10 cells a lane it holds both sums in a cell and is the faster
 // kernel for any number of clips.  With more cells it takes one sum at a time
 // (split), and the direct kernel's time grows with the clips instead: on the
-// Llama-3.1-8B layer set, INT3 g128 with 15 clips, split 727 us against 1172
+// Llama-3.1-8B layer set, INT3 g128 with 15 clips, split 709 us against 1172
 // direct (two passes over the weights); INT3 g64 with 10 clips 768 against
 // 987 (a pass of 12 at three wavefronts per SIMD); with 8 clips (INT4 g128,
-// one pass at four) 760 against 745.
+// one pass at four) 737 against 741, symmetric 719 against 643.
 bool int_cells_fit(int n_cells, int K, int group, bool any_fit, bool& split) {
   if (n_cells > 128 || n_cells + 2 > quasar::kCellThr) return false;
   split = int_cells_per_lane(n_cells, group, false) > quasar::int_cells_most(false);

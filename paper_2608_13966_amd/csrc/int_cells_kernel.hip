@@ -38,8 +38,9 @@
 // on that set: fp64 suffix sums, rounded cell by cell in two passes over the
 // LDS, and binning and atomics as two loops: 688 us; in integers, one pass in
 // registers, one loop, one compare per weight: 643; the fit's tests once per
-// group instead of once per clip: 635; h and h w swapped in odd cells: 634
-// (Qwen3-0.6B set, INT3 with 8 clips: 48.9, 42.0, 41.8, 41.2).
+// group instead of once per clip: 635; h and h w swapped in odd cells: 634; the staged
+// stores non-temporal: 624 (Qwen3-0.6B set, INT3 with 8 clips: 48.9, 42.0, 41.8,
+// 41.2, 39.9).
 // Forms.  Both sums in a cell (16 bytes) keep four workgroups on a compute
 // unit up to 10 cells a lane.  Beyond that the cells' LDS would leave two: the
 // SPLIT form takes h and then h w through 8-byte cells (each weight's cell is
