@@ -9,8 +9,8 @@
 //   q_k(u) = q0 + #{b in 1..NB : u >= T(k, b)},
 // with q0 = 0 and NB = qmax for asymmetric groups, q0 = -Q and NB = 2Q for
 // symmetric ones, and T(k, b) the least fp32 u whose code under clip k is at
-// least q0 + b.  The host finds every T(k, b) exactly, by bisection over the
-// ordered fp32 values with the kernels' own fp32 code recipe, and sorts the
+// least q0 + b.  The host finds every T(k, b) exactly, for the kernels' own fp32
+// code recipe, from one fp64 quotient and its neighbours, and sorts the
 // distinct ones, t_0 < ... < t_{M-1}.  The cell of u is #{i : t_i <= u} in
 // [0, M]; all K codes of a weight are fixed by its cell.  With
 // P_b = sum of h over the weights with u >= T(k, b) (a suffix sum over cells)
@@ -44,7 +44,7 @@
 // Forms.  Both sums in a cell (16 bytes) keep four workgroups on a compute
 // unit up to 10 cells a lane.  Beyond that the cells' LDS would leave two: the
 // SPLIT form takes h and then h w through 8-byte cells (each weight's cell is
-// kept, one byte).  INT3 g128 with 15 clips (93 cells), the Llama set: 716 us;
+// kept, one byte).  INT3 g128 with 15 clips (93 cells), the Llama set: 709 us;
 // both sums at once 1018; the direct kernel 1172.  A form with 8 weights per
 // lane (half the groups per wavefront, so half the LDS) took 750 us there,
 // and 59 against 45 us on the Qwen3-0.6B set (INT3, 8 clips): its per-group
