@@ -390,3 +390,49 @@ def test_int_path_choice():
     assert Q.quasar_int_path(_int_desc(fmt="nvfp4")) == Q.ERR_FORMAT
     assert Q.quasar_int_path(_int_desc(bits=5)) == Q.ERR_FORMAT
     assert Q.quasar_int_path(_int_desc(clips=(1.0, 1.5))) == Q.ERR_ARG
+
+
+class _ArrayLike:
+    def __array__(self, dtype=None, copy=None):
+        return np.array([1.0, 0.8], dtype=dtype or np.float64)
+
+
+def _readonly():
+    a = np.array([1.0, 0.9], dtype=np.float32)
+    a.flags.writeable = False
+    return a
+
+
+@pytest.mark.parametrize("clips", [
+    1.0, 1, np.float32(0.9), "0.9", b"12", [[1.0, 0.9], [0.8, 0.7]], ["1.0", "0.9"], (1, 0.9), [], [None], None,
+    _ArrayLike(), _readonly(), np.array(0.9), np.array([[1.0, 0.9]]), np.linspace(1, 0.5, 8)[::2],
+    np.array([1.0, 0.5], dtype=object), np.zeros(0, dtype=np.float32), tuple(np.linspace(1, 0.3, 20))],
+    ids=lambda c: type(c).__name__)
+def test_clips_take_what_numpy_takes(clips):
+    """Any form numpy makes a float32 array of gives that array's values, in its order."""
+    want = np.ascontiguousarray(np.asarray(clips, dtype=np.float32))
+    d = Q.Descriptor(64, 256, clips=clips)
+    assert d.desc.n_clips == want.size
+    np.testing.assert_array_equal([d.desc.clip_ratios[i] for i in range(want.size)], want.ravel())
+    assert d.clips.dtype == np.float32 and d.clips.shape == want.shape
+    np.testing.assert_array_equal(d.clips, want)
+
+
+@pytest.mark.parametrize("clips", [{1.0, 0.9}, {1.0: 1}, (f for f in (1.0,)), [1j]], ids=lambda c: type(c).__name__)
+def test_clips_refuse_what_numpy_refuses(clips):
+    with pytest.raises(TypeError):
+        Q.Descriptor(64, 256, clips=clips)
+
+
+def test_clips_are_the_callers_array():
+    """A contiguous float32 array is pointed to: an edit of it (or of d.clips)
+    is an edit of the descriptor; d.clips may be assigned and changes nothing."""
+    a = np.array([1.0, 0.9], dtype=np.float32)
+    d = Q.Descriptor(64, 256, clips=a)
+    a[1] = 0.5
+    assert d.desc.clip_ratios[1] == 0.5 and d.clips is a
+    d = Q.Descriptor(64, 256, clips=(1.0, 0.9))
+    d.clips[1] = 0.25
+    assert d.desc.clip_ratios[1] == 0.25
+    d.clips = np.ones(2, dtype=np.float32)
+    assert d.desc.clip_ratios[1] == 0.25
