@@ -436,3 +436,14 @@ def test_clips_are_the_callers_array():
     assert d.desc.clip_ratios[1] == 0.25
     d.clips = np.ones(2, dtype=np.float32)
     assert d.desc.clip_ratios[1] == 0.25
+
+
+def test_tensors_off_the_gpu_are_refused_as_torch_does():
+    """The current stream of a CPU tensor: torch's own error, type and text."""
+    import torch
+    W = torch.zeros(64, 256)
+    with pytest.raises(Exception) as want:
+        torch.cuda.current_stream(W.device)
+    with pytest.raises(want.type) as got:
+        Q.reconstruct(W, torch.zeros_like(W))
+    assert str(got.value) == str(want.value)
