@@ -74,7 +74,14 @@ class QuasarLinear(torch.nn.Module):
         g = weight.grad
         if g is None:
             raise RuntimeError("no gradient: call backward() first")
-        t = self.__dict__["t"] = self.t + 1  # an int: no module registration to look through
+        # Module.__setattr__ looks through every registration (1.5 us a name): a
+        # plain attribute is counted in place, and the results are assigned
+        # only when they are not the objects already there
+        own = self.__dict__
+        if "t" in own:
+            own["t"] += 1
+        else:  # a buffer of a subclass
+            self.t += 1
         W = weight.data
         out = self._out
         if out is None:
@@ -82,8 +89,8 @@ class QuasarLinear(torch.nn.Module):
             out = Q.alloc_outputs(d, W, want_r=False, want_diag=True, has_amax=True)
             out["r"] = self.r
             self._out = out
-        Q.adamw_reconstruct(W, self.m, self.v, g.contiguous(), step=t, out=out, r_dtype="bf16", **self.cfg,
+        Q.adamw_reconstruct(W, self.m, self.v, g.contiguous(), step=self.t, out=out, r_dtype="bf16", **self.cfg,
                             **self.hp)
-        if self.codes is not out["codes"] or self.scales is not out["scales"] or self.zeros is not out["zeros"]:
+        if any(own.get(k, own) is not out[k] for k in ("codes", "scales", "zeros")):
             self.codes, self.scales, self.zeros = out["codes"], out["scales"], out["zeros"]
         weight.grad = None
