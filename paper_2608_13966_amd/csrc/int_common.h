@@ -264,7 +264,10 @@ __device__ __forceinline__ bool int_score_ill(const IntMoments& mo, double s, do
 // A2 = sum h q w is ill-conditioned: the error bounds of the determinant
 // D = Sv A1 - A0^2 or of the numerator Sv A2 - A0 Svw exceed kFitTol of their
 // values, or D lies so close to the rank-deficiency threshold that its side
-// is not certain (symmetric: sum h q^2 and sum h q w against their bounds).
+// is not certain (symmetric: sum h q^2 and sum h q w against their bounds;
+// the binned kernel forms sum h q^2 as a difference, so all saliency on code 0
+// leaves a rest of either sign, or 0 where small terms fell below the fixed
+// point: only without fixed-point terms does 0 mean that every term is 0).
 // Perturbing h_i moves D by Sv ((q_i - qbar)^2 + var) <= 2 qmax^2 Sv per unit
 // of h_i, and the numerator by A2 - q_i Svw (|.| <= wabs (A0 + qmax Sv)) per
 // unit of h_i and by Sv q_j - A0 (|.| <= qmax Sv) per unit of h_j w_j; the
@@ -286,7 +289,7 @@ __device__ __forceinline__ bool int_fit_ill(const IntMoments& mo, double A0, dou
   // compile to a branch per test and clip
   if constexpr (SYM) {
     const double e1 = mo.qh * Q * Q + mo.rel * A1, e2 = mo.qhw * Q + mo.rel * mo.wabs * Q * mo.Sv;
-    return (A1 > 0.0) & ((e1 > kFitTol * A1) | (e2 > kFitTol * fabs(A2)));
+    return ((A1 != 0.0) | ((mo.qh != 0.0) & (mo.Sv != 0.0))) & ((e1 > kFitTol * A1) | (e2 > kFitTol * fabs(A2)));
   } else {
     const double Sv = mo.Sv;
     const double p1 = Sv * A1, p2 = A0 * A0;

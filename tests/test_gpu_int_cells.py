@@ -84,3 +84,20 @@ def test_exact_path_sees_updated_saliency(fmt, bits, group, k, w_bf16):
              clips=tuple(synth.clip_grid(1.0, 0.6, k)), w_bf16=w_bf16, ema=True,
              W=Wt.bfloat16() if w_bf16 else Wt, v=torch.from_numpy(v).cuda(), g=torch.from_numpy(g).cuda().bfloat16(),
              near_limit=rows * cols // group)
+
+
+@pytest.mark.parametrize("bits,group,k", [(2, 64, 8), (3, 64, 4), (3, 128, 8), (3, 128, 15), (4, 128, 8)])
+@pytest.mark.parametrize("rest", [0.0, 1e-25])
+def test_symmetric_groups_with_their_saliency_on_code_0(bits, group, k, rest):
+    """sum h q^2 is 0, or a saliency far below the fixed point's last place:
+    the scale is RTN's, or the one that saliency fixes.  The other saliencies
+    span e^+-20, so that the cell sums fill more than the 53 bits of an fp64."""
+    rows, cols = 64, 4 * group
+    rng = np.random.default_rng(k + group)
+    W = (rng.standard_normal((rows, cols)) * 1e-3).astype(np.float32)
+    v = np.exp(rng.standard_normal((rows, cols)) * 6).astype(np.float32)
+    W[:, ::group] = 0.37
+    v[:, ::group] = rest * v.max()
+    run_case(f"code0.int_sym{bits}.g{group}.K{k}.{rest}", rows, cols, 0, fmt="int_sym", bits=bits, group=group,
+             clips=tuple(synth.clip_grid(1.0, 0.65, k)), w_bf16=False, W=torch.from_numpy(W).cuda(),
+             v=torch.from_numpy(v).cuda())
