@@ -32,19 +32,33 @@ constexpr int N = kIntN;  // weights per lane
 // [-f m, f m] with m = max |w|, scale-only fit); otherwise asymmetric groups
 // (r = s q + z, q in [0, 2^BITS - 1], range [c - f rho, c + f rho]).
 //
-// Wavefronts per SIMD: symmetric groups have two moments a clip and their
-// saliencies are dead after the pass (the exact path reads them again), so 8
-// clips fit the 96 VGPRs of five and 12 the 128 of four; fp32 W is held in 8
-// more, and 2 of them spill.  Asymmetric groups at five spill 34 and lose
-// (Llama set, INT4 g128, 8 clips: symmetric 663 -> 643 us, asymmetric 728 -> 924).
-// At four, the saliencies' registers are worth 1 us to a launch that leaves one
-// wavefront per SIMD (INT3 g64 on 3.6 M weights: 20.5 -> 19.7 us).
-constexpr int int_direct_waves(int KC, bool multi, bool sym) {
-  if (sym) return KC > 8 || multi ? 4 : 5;
-  return KC > 8 || multi ? 3 : 4;
+// Wavefronts per SIMD: symmetric groups have two moments a clip, and 8 clips
+// fit the 96 VGPRs of five where their saliencies are dead after the pass (the
+// exact path reads them again): INT4 g128 on the Llama set, bf16 W, 663 ->
+// 643 us.  fp32 W is held in 8 registers more: with the EMA, five spill 1 to 4
+// and lose to four at every size (one matrix of 2^18 .. 2^25 weights, INT4 g64
+// 3-7%, INT3 g64 1-4%, INT4 g128 0-4%); without it they do not spill.
+// Asymmetric groups at five spill 34 and lose (INT4 g128, 728 -> 924).
+constexpr int int_direct_waves(int KC, bool multi, bool sym, bool w_bf16, int ema) {
+  if (KC > 8 || multi) return 3;
+  return sym && (w_bf16 || ema == 0) ? 5 : 4;
 }
+
+// Whether the exact path reads the saliencies again, so that their registers
+// are free from the pass on, or they are kept.  Reading costs a launch of a
+// few microseconds 0.1 us.  It is worth that for the AdamW step, whose stored
+// moments are live as well (INT4 g64, 8 clips: 2 or 3 spills without;
+// 1-3% on 2^18 .. 2^25 weights), for symmetric groups with 8 clips (the rule
+// above) and for asymmetric ones of 64 with 9 to 12 clips and no gradient (3%
+// from 2^21 weights on).  Elsewhere keeping them is the faster or the same: symmetric g128 with 9
+// to 12 clips 2-8%, asymmetric g64 with fp32 W and gradient 5%, small launches 1%.
+constexpr bool int_direct_rereads(int G, int KC, bool multi, bool sym, int ema) {
+  if (ema >= 3) return true;
+  return sym ? KC <= 8 && !multi : KC > 8 && G == 64 && ema == 0;
+}
+
 template <bool W_BF16, int EMA, int BITS, int G, int KC, bool MULTI, bool SYM>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(int_direct_waves(KC, MULTI, SYM))))
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(int_direct_waves(KC, MULTI, SYM, W_BF16, EMA))))
 void int_reconstruct_kernel(IntParams p) {
   constexpr int L = G / N;          // lanes per group
   constexpr int GPW = 64 / L;       // groups per wavefront
@@ -195,18 +209,22 @@ void int_reconstruct_kernel(IntParams p) {
   // a group whose fit the moments cannot fix accurately enough: every clip
   // again, straight from the weights
   {
-    // the saliencies again, so that their registers are free in between: v'
-    // when this kernel stored it, written by another lane of this wavefront,
-    // which the workgroup-scope fences make visible
+    // read again: v' when this kernel stored it, written by another lane of
+    // this wavefront, which the workgroup-scope fences make visible
     auto load_h = [&](float (&hv)[N]) {
-      if constexpr (EMA != 0) {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-      }
-      load16<false>(mtx.v, e0, hv);
+      if constexpr (int_direct_rereads(G, KC, MULTI, SYM, EMA)) {
+        if constexpr (EMA != 0) {
+          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+          __builtin_amdgcn_wave_barrier();
+          __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+        }
+        load16<false>(mtx.v, e0, hv);
 #pragma unroll
-      for (int i = 0; i < N; i++) hv[i] = weight_of(hv[i], p.weighting);
+        for (int i = 0; i < N; i++) hv[i] = weight_of(hv[i], p.weighting);
+      } else {
+#pragma unroll
+        for (int i = 0; i < N; i++) hv[i] = v[i];
+      }
     };
     const bool ill = run_max<L>(best.ill ? 1.0f : 0.0f) > 0.0f;
     int_exact_wave<L, SYM, QMAX, false, W_BF16>(p, wr, load_h, rg, s_alpha, s_clip, lane,

@@ -30,7 +30,7 @@ def _inputs(rows, cols, seed, w_bf16, g_fp32):
 
 
 def run_step(name, W, m, v, g, *, step, fmt="int", bits=4, group=128, clips=(1.0, 0.8, 0.6), r_dtype="bf16",
-             weighting="h", row_step=1, amax=None):
+             weighting="h", row_step=1, amax=None, near_limit=None):
     """One fused step on the GPU tensors (updated in place) and on host copies
     through the oracle; compares every output.  Returns the oracle dict."""
     Wh, mh, vh, gh = host(W), host(m), host(v), host(g)
@@ -75,7 +75,8 @@ def run_step(name, W, m, v, g, *, step, fmt="int", bits=4, group=128, clips=(1.0
     fails, st = _parity.compare(fmt=fmt, bits=bits, group=group, W=o["W_out"], h=h, o=o, gpu=gpu)
     record(name, st)
     assert not fails, "\n".join(fails)
-    assert st["near_tie"] + st["near_e4m3"] <= max(2, 0.001 * st["groups"]), dict(st)
+    limit = max(2, 0.001 * st["groups"]) if near_limit is None else near_limit
+    assert st["near_tie"] + st["near_e4m3"] <= limit, dict(st)
     return o
 
 
@@ -120,6 +121,29 @@ def test_fused_adamw_llama_gate_sampled(fmt, bits, group):
              row_step=97, amax=amax)
     del W, m, v, g
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("bits,group,k", [(4, 128, 8), (4, 64, 12), (3, 64, 16), (2, 64, 12), (3, 128, 15)])
+@pytest.mark.parametrize("wb", [False, True])
+def test_exact_path_after_the_step(bits, group, k, wb):
+    """Groups whose moments cannot fix the fit are evaluated from saliencies
+    that the kernel reads again after the step stored them (in either INT
+    kernel).  The gradient puts nearly all of v' on another weight than v
+    has it on; with it on one code, clips may tie."""
+    rows, cols = 5, 3 * group
+    rng = np.random.default_rng(k + group)
+    W = torch.from_numpy((rng.standard_normal((rows, cols)) * 0.02).astype(np.float32)).cuda()
+    v = rng.random((rows, cols)).astype(np.float32) / group
+    g = np.zeros((rows, cols), dtype=np.float32)
+    n = rows * cols // group
+    for i in range(n):
+        at = i * group + rng.integers(1, group)
+        v.flat[at - 1] = 1.0
+        v.flat[i * group:(i + 1) * group] *= np.float32(10.0 ** -(6 + i % 4))
+        g.flat[at] = 32.0
+    run_step(f"adamw.exact.int{bits}.g{group}.K{k}.{wb}", W.bfloat16() if wb else W, torch.zeros_like(W),
+             torch.from_numpy(v).cuda(), torch.from_numpy(g).cuda().bfloat16(), step=3, bits=bits, group=group,
+             clips=tuple(synth.clip_grid(1.0, 0.6, k)), near_limit=n)
 
 
 def test_fused_adamw_error_leaves_state_untouched():
