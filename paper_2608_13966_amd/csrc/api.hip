@@ -555,6 +555,16 @@ int launch_path(const quasar_desc* d, const void* W, void* Wu, float* m, float* 
   const int K = d->n_clips;
   const float beta2 = ema_mode >= 3 ? d->beta2 : (g ? d->beta2 : 0.0f);
   const float omb2 = 1.0f - beta2;
+  // bytes the launch reads and writes, the outputs per group left out
+  int64_t weights = d->rows * d->cols;
+  if (batch) {
+    weights = 0;
+    for (int i = 0; i < batch->n; i++) weights += batch->s[i].n_units * (is_rubin(d) ? 512 : group_of(d));
+  }
+  const int64_t footprint = weights * ((w_bf16 ? 2 : 4) + 4 + (g ? (d->g_dtype == QUASAR_BF16 ? 2 : 4) : 0) +
+                                       (m ? 4 : 0) + (r ? (r_bf16 ? 2 : 4) : 0));
+  const quasar::StorePolicy store = quasar::store_policy(footprint);
+  if (ema_mode >= 3 && store == quasar::kStoreStreaming) ema_mode += 2;  // the kernels' modes 5 and 6
   hipError_t e;
   if (d->format == QUASAR_INT || d->format == QUASAR_INT_SYM) {
     const bool sym = d->format == QUASAR_INT_SYM;
@@ -582,6 +592,7 @@ int launch_path(const quasar_desc* d, const void* W, void* Wu, float* m, float* 
     if (adam) p.adam = *adam;
     p.r_bf16 = r_bf16;
     if (batch) p.batch = *batch;
+    p.store = store;
     int_cells(p, K, d->bits, sym, d->group);
     e = quasar::launch_int(p, d->bits, d->group, w_bf16, ema_mode, st);
   } else if (is_rubin(d)) {
@@ -604,6 +615,7 @@ int launch_path(const quasar_desc* d, const void* W, void* Wu, float* m, float* 
     p.weighting = d->weighting;
     rubin_clip_tables(d, p);
     rubin_thresholds(p, K);
+    p.stream_r = footprint >= 2 * quasar::kLastLevelCache;
     if (batch) p.batch = *batch;
     e = quasar::launch_rubin(p, w_bf16, ema_mode, st);
   } else {

@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace quasar {
 
 // ---- bit casts -------------------------------------------------------------
@@ -92,8 +94,19 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ uint4 ld128_nt(const void* p) {
   return __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p)));
 }
+
 __device__ __forceinline__ void st128_nt(void* p, uint4 v) {
   __builtin_nontemporal_store(__builtin_bit_cast(u32x4, v), reinterpret_cast<u32x4*>(p));
+}
+
+// A wavefront's buffer of `bytes` bytes at p (both uniform), and a store at
+// offset `at` of it that is written through the L2 at once (device scope);
+// one at or past the buffer's end does nothing.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t wave_buffer(void* p, int bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(p, 0, bytes, 0x00027000);  // raw, 32-bit elements
+}
+__device__ __forceinline__ void st128_through(__amdgpu_buffer_rsrc_t b, int at, uint4 v) {
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), b, at, 0, 16 /* sc1 */);
 }
 
 // Load N = 16 consecutive elements of a fp32 or bf16 tensor as fp32.
@@ -412,6 +425,22 @@ __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// How whole lines that a launch writes through LDS (wave_flush) are stored:
+//   through    written through the L2 at once; they stay in the last-level
+//              cache for whatever reads them next;
+//   streaming  non-temporal.
+// bf16 W without the AdamW step streams.  fp32 W and the step stream when what
+// the launch reads and writes does not fit the last-level cache.  One matrix of
+// 2^20 to 2^26 weights, INT2 to INT4, in each mode, in cached sizes through
+// against streaming: the AdamW step 1.02 to 1.11 times as fast (it finds m, v and W in
+// that cache the next time); fp32 W the pass alone 1.00 to 1.04 times, the pass
+// and a reader of r 1.04 to 1.08 times.  Beyond: fp32 AdamW on 2^24 weights
+// streams 1.12 times as fast, fp32 W 1.03.  bf16 W, streaming against plain
+// stores: the pass alone 1.00 to 1.07 times as fast, with a reader of r 0.97 to 1.05.
+enum StorePolicy : int { kStoreThrough = 0, kStoreStreaming = 1 };
+constexpr int64_t kLastLevelCache = 256ll << 20;  // bytes
+constexpr StorePolicy store_policy(int64_t bytes) { return bytes < kLastLevelCache ? kStoreThrough : kStoreStreaming; }
+
 // ---- coalesced stores of a wavefront's stretch of a tensor -------------------
 // A wavefront whose lanes hold 16 consecutive elements each covers one
 // contiguous stretch of 1024 elements: lane l's 16 start at element
@@ -427,10 +456,17 @@ __device__ __forceinline__ void wave_lds_fence() {
 struct WaveImage {
   uint4* stage;  // this wavefront's LDS area: wave_stage_chunks() chunks of 16 bytes
   int64_t e0;    // the stretch's first element
-  int64_t n;     // how many of its 1024 elements exist (<= 0: none)
+  int n;         // how many of its 1024 elements exist
+  int store;     // the launch's StorePolicy (uniform)
   int idx;       // this lane's 16 elements start at element 16 idx of the stretch
   int lane;
 };
+
+// left: the elements from e0 to the tensor's end
+__device__ __forceinline__ WaveImage wave_image(void* stage, int64_t e0, int64_t left, int store, int idx, int lane) {
+  const int n = left < 0 ? 0 : left < 1024 ? (int)left : 1024;
+  return WaveImage{reinterpret_cast<uint4*>(stage), e0, n, store, idx, lane};
+}
 
 template <int ESZ, int PER>
 __host__ __device__ constexpr int wave_stage_chunks() {
@@ -438,48 +474,73 @@ __host__ __device__ constexpr int wave_stage_chunks() {
 }
 
 // Every lane of the wavefront takes part; `base` is the tensor (16-byte
-// aligned), and elements of the stretch at or past n are not written.
+// aligned), and elements of the stretch at or past its end are not written.
 // wave_put writes the lane's chunk c (c < ESZ: its elements 16 c / ESZ
 // onwards) into the stage, after a wave_lds_fence() that follows any earlier
 // use of the stage; wave_flush then stores the whole stretch and leaves the
 // stage free.  wave_store does both for the lane's 16 elements given as
-// 4 ESZ dwords in element order.  The stores are non-temporal: whole lines that
-// nothing reads again soon (Llama set, us: INT2 g64 12 clips 630 -> 624, INT2
-// with the AdamW step 1164 -> 1158; Qwen3-0.6B INT3 40.8 -> 39.9).
+// 4 ESZ dwords in element order.
+//
 template <int ESZ, int PER>
 __device__ __forceinline__ void wave_put(const WaveImage& im, int c, uint4 x) {
   const int ch = im.idx * ESZ + c;
   im.stage[ch + ch / PER] = x;
 }
-template <int ESZ, int PER>
+template <int ESZ, int PER, int POLICY>
 __device__ __forceinline__ void wave_flush(const WaveImage& im, void* base) {
   static_assert(ESZ == 2 || ESZ == 4, "bf16 or fp32 elements");
   wave_lds_fence();
+  uint4* const out = reinterpret_cast<uint4*>(base) + (im.e0 * ESZ) / 16;
+  __amdgpu_buffer_rsrc_t through;
+  if constexpr (POLICY == kStoreThrough) through = wave_buffer(out, im.n * ESZ);
   // one chunk in flight at a time: fewer live registers than reading all
   // chunks first, which the kernels around this cannot spare
-  uint4* out = reinterpret_cast<uint4*>(base) + (im.e0 * ESZ) / 16;
 #pragma unroll
   for (int t = 0; t < ESZ; t++) {
     const int ch = im.lane + 64 * t;
     const uint4 x = im.stage[ch + ch / PER];
-    if ((int64_t)ch * (16 / ESZ) < im.n) st128_nt(out + ch, x);
+    if constexpr (POLICY == kStoreThrough) {
+      st128_through(through, 16 * ch, x);
+      __builtin_amdgcn_sched_barrier(0);
+    } else {
+      if (ch * (16 / ESZ) < im.n) st128_nt(out + ch, x);
+    }
   }
   wave_lds_fence();
 }
-template <int ESZ, int PER>
+template <int ESZ, int PER, int POLICY>
 __device__ __forceinline__ void wave_store(const WaveImage& im, void* base, const uint32_t (&d)[4 * ESZ]) {
   wave_lds_fence();  // earlier reads of the stage by this wavefront are done
 #pragma unroll
   for (int c = 0; c < ESZ; c++) wave_put<ESZ, PER>(im, c, make_uint4(d[4 * c], d[4 * c + 1], d[4 * c + 2], d[4 * c + 3]));
-  wave_flush<ESZ, PER>(im, base);
+  wave_flush<ESZ, PER, POLICY>(im, base);
 }
 
-template <int PER>
+template <int PER, int POLICY>
 __device__ __forceinline__ void wave_store_f32(const WaveImage& im, float* base, const float (&x)[16]) {
   uint32_t d[16];
 #pragma unroll
   for (int i = 0; i < 16; i++) d[i] = as_u32(x[i]);
-  wave_store<4, PER>(im, base, d);
+  wave_store<4, PER, POLICY>(im, base, d);
+}
+
+// f(std::integral_constant<int, POLICY>) for the launch's policy.  The AdamW
+// step's kernels have it in their mode (EMA 3 and 4 through, 5 and 6
+// streaming): a branch around their stores cost large sets 1 to 3%.  fp32 W
+// without the step takes one branch around all the stores that f makes.
+template <bool W_BF16, int EMA, typename F>
+__device__ __forceinline__ void with_policy(const WaveImage& im, F f) {
+  constexpr std::integral_constant<int, kStoreThrough> through;
+  constexpr std::integral_constant<int, kStoreStreaming> streaming;
+  if constexpr (EMA >= 5 || (EMA < 3 && W_BF16)) {
+    f(streaming);
+  } else if constexpr (EMA >= 3) {
+    f(through);
+  } else if (im.store == kStoreStreaming) {
+    f(streaming);
+  } else {
+    f(through);
+  }
 }
 
 }  // namespace quasar

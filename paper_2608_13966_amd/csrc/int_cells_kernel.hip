@@ -192,7 +192,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
   const int cpl = p.cells.cpl;
   const int wave_bytes = (int)int_cells_wave_bytes(G, SPLIT, cpl);
   u64* const s_wave = s_hist + wave * (wave_bytes / 8);
-  const WaveImage im = int_image<L>(s_wave, wave_g0, mtx.n_groups, slot, j, lane);
+  const WaveImage im = int_image<L>(s_wave, wave_g0, mtx.n_groups, slot, j, lane, p.store);
 
   WRegs<W_BF16> wr;
   float v[N];
@@ -576,7 +576,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
                                                   best);
   }
 
-  int_finish<W_BF16, BITS, G, SYM, kSpread>(p, mtx, wr, rg, mo.Sv, best, s_alpha, s_win[wave][slot], j, gid, im,
+  int_finish<W_BF16, EMA, BITS, G, SYM, kSpread>(p, mtx, wr, rg, mo.Sv, best, s_alpha, s_win[wave][slot], j, gid, im,
                                          active);
 }
 
@@ -628,6 +628,8 @@ hipError_t launch_w(const IntParams& p, int bits, int group, int ema_mode, hipSt
     case 2: return launch_e<W_BF16, 2>(p, bits, group, s);
     case 3: return launch_e<W_BF16, 3>(p, bits, group, s);
     case 4: return launch_e<W_BF16, 4>(p, bits, group, s);
+    case 5: return launch_e<W_BF16, 5>(p, bits, group, s);
+    case 6: return launch_e<W_BF16, 6>(p, bits, group, s);
     default: return launch_e<W_BF16, 0>(p, bits, group, s);
   }
 }

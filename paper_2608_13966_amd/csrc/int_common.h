@@ -100,10 +100,10 @@ __host__ __device__ constexpr int int_stage_bytes() { return 16 * wave_stage_chu
 // The wavefront's stretch of the matrix: groups wave_g0 .. wave_g0 + 64 / L - 1.
 template <int L>
 __device__ __forceinline__ WaveImage int_image(void* stage, int64_t wave_g0, int64_t n_groups, int slot, int j,
-                                               int lane) {
+                                               int lane, int store) {
   constexpr int G = L * kIntN;
   const int64_t left = (n_groups - wave_g0) * G;
-  return WaveImage{reinterpret_cast<uint4*>(stage), wave_g0 * G, left < 1024 ? left : 1024, slot * L + j, lane};
+  return wave_image(stage, wave_g0 * G, left, store, slot * L + j, lane);
 }
 
 // Load the lane's 16 weights and saliencies (each byte of W, v, g once, with
@@ -127,23 +127,26 @@ __device__ __forceinline__ void int_load(const IntParams& p, const IntMatrix& mt
       float u = p.omb2 * t;
       v[i] = __builtin_fmaf(p.beta2, v[i], u);
     }
-    wave_store_f32<P4>(im, mtx.v, v);
+    with_policy<W_BF16, EMA>(im, [&](auto pol) { wave_store_f32<P4, decltype(pol)::value>(im, mtx.v, v); });
   } else if constexpr (EMA >= 3) {
     // one AdamW step first; the updated W is reconstructed and the updated
     // second moment is the saliency
     float g[kIntN], m[kIntN], w[kIntN];
-    load16<EMA == 3>(mtx.g, e0, g);
+    load16<EMA == 3 || EMA == 5>(mtx.g, e0, g);
     load16<false>(mtx.m, e0, m);
 #pragma unroll
     for (int i = 0; i < kIntN; i++) w[i] = wr.get(i);
     adamw16(w, m, v, g, p.adam, p.beta2, p.omb2);
     wr.set(w);  // bf16 W: rounded here, and the rounded value is reconstructed
-    wave_store_f32<P4>(im, mtx.v, v);
-    wave_store_f32<P4>(im, mtx.m, m);
-    if constexpr (W_BF16)
-      wave_store<2, P2>(im, mtx.Wu, wr.d);
-    else
-      wave_store_f32<P4>(im, static_cast<float*>(mtx.Wu), wr.f);
+    with_policy<W_BF16, EMA>(im, [&](auto pol) {
+      constexpr int POL = decltype(pol)::value;
+      wave_store_f32<P4, POL>(im, mtx.v, v);
+      wave_store_f32<P4, POL>(im, mtx.m, m);
+      if constexpr (W_BF16)
+        wave_store<2, P2, POL>(im, mtx.Wu, wr.d);
+      else
+        wave_store_f32<P4, POL>(im, static_cast<float*>(mtx.Wu), wr.f);
+    });
   }
   if (p.weighting != 0) {
 #pragma unroll
@@ -541,7 +544,7 @@ __device__ __forceinline__ void int_fit_score(const IntParams& p, int k, float f
 // broadcast through `win` (this group's 4 floats of LDS), then the emit:
 // codes of f*, r = fmaf(s, q, z) in W's dtype (or fp32 r), (s, z) and the
 // optional diagnostics.
-template <bool W_BF16, int BITS, int G, bool SYM, bool SPREAD = false>
+template <bool W_BF16, int EMA, int BITS, int G, bool SYM, bool SPREAD = false>
 __device__ __forceinline__ void int_finish(const IntParams& p, const IntMatrix& mtx, const WRegs<W_BF16>& wr,
                                            const IntRange& g, double Sv, const IntBest& best, const float* s_alpha,
                                            float* win, int j, int64_t gid, const WaveImage& im, bool active) {
@@ -615,10 +618,12 @@ __device__ __forceinline__ void int_finish(const IntParams& p, const IntMatrix& 
     }
   }
   if (mtx.r) {
-    if (r_bf16)
-      wave_flush<2, P2>(im, mtx.r);
-    else
-      wave_flush<4, P4>(im, mtx.r);
+    with_policy<W_BF16, EMA>(im, [&](auto pol) {
+      if (r_bf16)
+        wave_flush<2, P2, decltype(pol)::value>(im, mtx.r);
+      else
+        wave_flush<4, P4, decltype(pol)::value>(im, mtx.r);
+    });
   }
   // INT3: members 2i and 2i + 1 hold bits [96 i, 96 i + 96) of the group's
   // stream, three whole dwords; the even member needs the odd one's low bits

@@ -100,7 +100,7 @@ void int_reconstruct_kernel(IntParams p) {
   if (!active) gid = mtx.n_groups - 1;  // recompute the last group; nothing is stored
   const int64_t e0 = gid * G + (int64_t)j * N;
   double* red = s_red[wave];
-  const WaveImage im = int_image<L>(red, wave_g0, mtx.n_groups, slot, j, lane);
+  const WaveImage im = int_image<L>(red, wave_g0, mtx.n_groups, slot, j, lane, p.store);
 
   // W stays in its storage format in registers (bf16: 8 dwords) and is widened
   // on use, which keeps the kernel inside 128 VGPRs (4 waves per SIMD).
@@ -231,7 +231,7 @@ void int_reconstruct_kernel(IntParams p) {
                                                 ill && active && !rg.constant, reinterpret_cast<float*>(red), best);
   }
 
-  int_finish<W_BF16, BITS, G, SYM>(p, mtx, wr, rg, mo.Sv, best, s_alpha, s_win[wave][slot], j, gid, im, active);
+  int_finish<W_BF16, EMA, BITS, G, SYM>(p, mtx, wr, rg, mo.Sv, best, s_alpha, s_win[wave][slot], j, gid, im, active);
 }
 
 template <bool W_BF16, int EMA, int BITS, int G>
@@ -288,6 +288,8 @@ hipError_t launch_e(const IntParams& p, int bits, int group, int ema_mode, hipSt
     case 2: return launch_b<W_BF16, 2>(p, bits, group, s);
     case 3: return launch_b<W_BF16, 3>(p, bits, group, s);
     case 4: return launch_b<W_BF16, 4>(p, bits, group, s);
+    case 5: return launch_b<W_BF16, 5>(p, bits, group, s);
+    case 6: return launch_b<W_BF16, 6>(p, bits, group, s);
     default: return launch_b<W_BF16, 0>(p, bits, group, s);
   }
 }

@@ -127,7 +127,7 @@ void nvfp4_reconstruct_kernel(Nvfp4Params p) {
   } else if constexpr (EMA >= 3) {
     // one AdamW step first (see int_kernel.hip)
     float g[N], m[N], w[N];
-    load16<EMA == 3>(mtx.g, e0, g);
+    load16<EMA == 3 || EMA == 5>(mtx.g, e0, g);
     load16<false>(mtx.m, e0, m);
 #pragma unroll
     for (int i = 0; i < N; i++) w[i] = wr.get(i);
@@ -136,13 +136,16 @@ void nvfp4_reconstruct_kernel(Nvfp4Params p) {
     const int wave = wave_index();
     const int64_t wave_b0 = blk * kThreads + 64 * wave;  // the wavefront's first block
     const int64_t left = (mtx.n_blocks - wave_b0) * N;
-    const WaveImage im = {s_stage[wave], wave_b0 * N, left < 64 * N ? left : 64 * N, tid & 63, tid & 63};
-    wave_store_f32<4>(im, mtx.v, v);
-    wave_store_f32<4>(im, mtx.m, m);
-    if constexpr (W_BF16)
-      wave_store<2, 2>(im, mtx.Wu, wr.d);
-    else
-      wave_store_f32<4>(im, static_cast<float*>(mtx.Wu), wr.f);
+    const WaveImage im = wave_image(s_stage[wave], wave_b0 * N, left, 0, tid & 63, tid & 63);
+    with_policy<W_BF16, EMA>(im, [&](auto pol) {
+      constexpr int POL = decltype(pol)::value;
+      wave_store_f32<4, POL>(im, mtx.v, v);
+      wave_store_f32<4, POL>(im, mtx.m, m);
+      if constexpr (W_BF16)
+        wave_store<2, 2, POL>(im, mtx.Wu, wr.d);
+      else
+        wave_store_f32<4, POL>(im, static_cast<float*>(mtx.Wu), wr.f);
+    });
   }
   if (p.weighting != 0) {  // h = v, v*v or 1 (uniform branch)
 #pragma unroll
@@ -373,7 +376,6 @@ __device__ __forceinline__ float chunk_absmax(uint4 t) {
 // loads chunks t, t + 256, ... (each load instruction reads 1 KB contiguous per
 // wavefront), kAbsBatch loads in flight at a time; then a DPP / LDS maximum
 // and at most one atomicMax on the fp32 bit pattern per workgroup.
-constexpr int64_t kLastLevelCache = 256ll << 20;  // bytes
 constexpr int64_t kAbsChunks = (int64_t)kThreads * kAbsSpan;
 
 //
@@ -482,6 +484,8 @@ hipError_t launch_e(const Nvfp4Params& p, int ema_mode, hipStream_t s) {
     case 2: return launch_kc<W_BF16, 2>(p, s);
     case 3: return launch_kc<W_BF16, 3>(p, s);
     case 4: return launch_kc<W_BF16, 4>(p, s);
+    case 5: return launch_kc<W_BF16, 5>(p, s);
+    case 6: return launch_kc<W_BF16, 6>(p, s);
     default: return launch_kc<W_BF16, 0>(p, s);
   }
 }

@@ -138,6 +138,7 @@ struct IntParams {
   int weighting;        // 0 h = v, 1 h = v*v, 2 h = 1
   int param_dtype;      // 0 fp32, 1 bf16, 2 fp16 (quasar_dtype values)
   int symmetric;        // 1: symmetric groups (alpha = Q / f; zeros optional, written 0)
+  int store;            // StorePolicy
   float alpha[kMaxClips];  // qmax / (2 f_k) (symmetric: Q / f_k), fp32 division on the host
   float clip[kMaxClips];   // f_k
   // fused AdamW step (ema modes 3 and 4): W is updated in place through Wu,
@@ -217,6 +218,7 @@ struct RubinParams {
   // kernel sum its block's code-3 and code-4 entries directly.
   int buckets;
   int cmax;
+  int stream_r;  // bf16 r: non-temporal stores
   float unsafe_lo, unsafe_hi;
   uint8_t base[kCellBuckets];
   BatchTable batch;

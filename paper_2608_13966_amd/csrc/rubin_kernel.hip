@@ -56,7 +56,7 @@
 // three fmas (six instructions before), the argmin taken once over all clips,
 // the tie and lost-saliency tests made by one unsigned minimum each, and the
 // codes emitted as bytes that permute the codebook (no LDS lookup per weight),
-// 718 before whole lines were loaded and stored non-temporally.
+// 718 before whole lines of W and g were loaded non-temporally.
 #include <type_traits>
 
 #include "device_common.h"
@@ -188,8 +188,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5))) v
 
   // ---- load (each byte once), optional fused EMA, weighting ------------------
   float w[NE], v[NE];
-  // bf16 W and g, and a bf16 r: 8 lanes' 16 bytes are one row of the block, a
-  // whole line, so they pass by the caches (Llama set: 718 -> 711 us)
+  // bf16 W and g: 8 lanes' 16 bytes are one row of the block, a whole line, so
+  // they pass by the caches (with r's stores, Llama set: 718 -> 711 us)
   if constexpr (W_BF16) {
     const uint4 t = ld128_nt(reinterpret_cast<const uint16_t*>(mtx.W) + e0);
     const uint32_t d[4] = {t.x, t.y, t.z, t.w};
@@ -521,9 +521,17 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5))) v
   }
   if (mtx.r) {
     if constexpr (W_BF16) {
-      st128_nt(reinterpret_cast<uint16_t*>(mtx.r) + e0,
-            make_uint4(pack_bf16x2(r[0], r[1]), pack_bf16x2(r[2], r[3]), pack_bf16x2(r[4], r[5]),
-                       pack_bf16x2(r[6], r[7])));
+      // r is what is read next: plain stores until the set is far larger than
+      // the last-level cache (one matrix, bf16 g, the pass and a reader of r:
+      // 2^25 weights 151 us with non-temporal stores, 144 without, the pass
+      // alone the same; Llama set, the pass alone 725 and 731)
+      const uint4 x = make_uint4(pack_bf16x2(r[0], r[1]), pack_bf16x2(r[2], r[3]), pack_bf16x2(r[4], r[5]),
+                                 pack_bf16x2(r[6], r[7]));
+      uint16_t* const dst = reinterpret_cast<uint16_t*>(mtx.r) + e0;
+      if (p.stream_r)
+        st128_nt(dst, x);
+      else
+        st128(dst, x);
     } else {
       float* rp = reinterpret_cast<float*>(mtx.r) + e0;
       st128(rp, make_uint4(as_u32(r[0]), as_u32(r[1]), as_u32(r[2]), as_u32(r[3])));
