@@ -91,6 +91,7 @@ class QuasarLinear(torch.nn.Module):
             self._out = out
         Q.adamw_reconstruct(W, self.m, self.v, g.contiguous(), step=self.t, out=out, r_dtype="bf16", **self.cfg,
                             **self.hp)
-        if any(own.get(k, own) is not out[k] for k in ("codes", "scales", "zeros")):
+        if (own.get("codes", own) is not out["codes"] or own.get("scales", own) is not out["scales"]
+                or own.get("zeros", own) is not out["zeros"]):
             self.codes, self.scales, self.zeros = out["codes"], out["scales"], out["zeros"]
         weight.grad = None
