@@ -36,6 +36,26 @@ def test_workspace_absmax_matches_supplied(rows, cols, w_bf16, where):
         assert torch.equal(a[k], b[k]), k
 
 
+@pytest.mark.parametrize("rows,cols", SHAPES)
+@pytest.mark.parametrize("g_fp32", [False, True])
+def test_workspace_absmax_with_the_ema(rows, cols, g_fp32):
+    """After the fused EMA the same load reads the partial maxima or the one value."""
+    W, v, g = synth.gen_matrix(rows, cols, 11, w_bf16=True, ema=True, device="cuda")
+    g = g.float() if g_fp32 else g
+    amax = torch.zeros(4, device="cuda")
+    amax[0] = W.abs().max()
+    kw = dict(fmt="nvfp4", clips=(1.0, 0.9, 0.8))
+    va, vb = v.clone(), v.clone()
+    a = Q.reconstruct(W, v.clone(), g, **kw)
+    a["workspace"].fill_(0xFF)
+    a = Q.reconstruct(W, va, g, out=a, **kw)
+    b = Q.reconstruct(W, vb, g, tensor_amax=amax, **kw)
+    torch.cuda.synchronize()
+    assert torch.equal(va, vb) and float(a["tensor_scale"][0]) == float(b["tensor_scale"][0])
+    for k in ("codes", "scales", "r", "best_clip", "err"):
+        assert torch.equal(a[k], b[k]), k
+
+
 @pytest.mark.parametrize("rows", [8192, 8193])  # 256 MiB of bf16 W, the last with cached loads, and the next
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 def test_absmax_around_the_last_level_cache(rows, dtype):
