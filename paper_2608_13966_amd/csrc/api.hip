@@ -883,8 +883,13 @@ int quasar_adamw_reconstruct_batch(const quasar_desc* d, const quasar_adamw* opt
   const int s = quasar_adamw_batch_check(d, opt, mats, n_mats, r_dtype);
   if (s != QUASAR_OK) return s;
   const quasar_adamw_matrix& x0 = mats[0];
+  // the shared fields come from the descriptor; slot 0 also fills the
+  // single-matrix fields (the by-products are the slots')
+  quasar_desc d0 = *d;
+  d0.rows = x0.rows;
+  d0.cols = x0.cols;
   if (n_mats == 1)
-    return quasar_adamw_reconstruct(d, opt, x0.W, x0.m, x0.v, x0.g, x0.codes, x0.scales, x0.zeros, x0.r, r_dtype,
+    return quasar_adamw_reconstruct(&d0, opt, x0.W, x0.m, x0.v, x0.g, x0.codes, x0.scales, x0.zeros, x0.r, r_dtype,
                                     x0.best_clip, x0.err, x0.tensor_scale, x0.tensor_amax, x0.amax_out, stream);
   const hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   quasar::BatchTable bt;
@@ -922,11 +927,6 @@ int quasar_adamw_reconstruct_batch(const quasar_desc* d, const quasar_adamw* opt
     bt.total_blocks += (ms.n_units + upb - 1) / upb;
   }
   if (clear.n > 0 && quasar::launch_clear_all(clear, st) != hipSuccess) return QUASAR_ERR_DEVICE;
-  // the shared fields come from the descriptor; slot 0 also fills the
-  // single-matrix fields (the by-products are the slots')
-  quasar_desc d0 = *d;
-  d0.rows = x0.rows;
-  d0.cols = x0.cols;
   d0.beta2 = opt->beta2;
   const quasar::AdamWConsts a = adamw_consts(opt);
   const int ema_mode = d0.g_dtype == QUASAR_BF16 ? 3 : 4;

@@ -170,3 +170,22 @@ def test_batch_nvfp4_amax_from_batched_pass():
     torch.cuda.synchronize()
     for i, (a, b) in enumerate(zip(singles, outs)):
         _same(f"nvfp4.auto.{i}", a, b)
+
+
+def test_adamw_batch_of_one_takes_the_matrix_shape():
+    """The descriptor's rows and cols are ignored, with one matrix as with more."""
+    clips = tuple(float(x) for x in synth.clip_grid(1.0, 0.6, 8))
+    W, v, g = synth.gen_matrix(9, 384, 5, w_bf16=False, ema=True, device="cuda")
+    m, v = synth.gen_adamw_state(9, 384, 5, v, device="cuda")
+    one = [t.clone() for t in (W, m, v, g)]
+    want = Q.adamw_reconstruct(*one, lr=1e-3, step=2, bits=4, group=128, clips=clips, r_dtype="bf16")
+    d = Q.Descriptor(1, 128, bits=4, group=128, clips=clips, w_dtype=Q.F32, g_dtype=Q.BF16)
+    o = dict(Q.alloc_outputs(want["desc"], W, want_r=False), r=torch.empty_like(W, dtype=torch.bfloat16))
+    mat = Q.AdamWMatrix(9, 384, *(Q._p(x) for x in (W, m, v, g, o["codes"], o["scales"], o["zeros"], o["r"],
+                                                  o["best_clip"], o["err"], None, None, None)))
+    assert Q.quasar_adamw_reconstruct_batch(d, Q.AdamW(1e-3, 0.9, 0.999, 1e-8, 0.0, 2), [mat], Q.BF16,
+                                            torch.cuda.current_stream().cuda_stream) == Q.OK
+    torch.cuda.synchronize()
+    _same("adamw.one", want, o, keys=("codes", "scales", "zeros", "r", "best_clip", "err"))
+    for a, b in zip(one[:3], (W, m, v)):
+        assert torch.equal(a.view(torch.int32), b.view(torch.int32))
