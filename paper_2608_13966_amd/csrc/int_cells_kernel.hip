@@ -138,7 +138,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
   constexpr int NB = SYM ? 2 * QMAX : QMAX;  // code steps per clip
   constexpr int OWN = kMaxClips / L;         // clips a lane may own
   constexpr int CELL = SPLIT ? 8 : 16;       // bytes
-  constexpr int CMOST = int_cells_most(SPLIT);
   static_assert(2 * kThreads == kIntBuckets && kThreads == kCellBuckets && kThreads == kMaxClips * kCellSteps, "table entries per thread");
   static_assert((size_t)int_stage_bytes<kSpread, G>() == int_cells_stage_bytes(G), "the launch sizes the stage");
 
@@ -599,9 +598,12 @@ hipError_t launch_s(const IntParams& p, hipStream_t s) {
   return hipGetLastError();
 }
 
+// INT2: at most 3 thresholds a clip, the tie ones merged into two, 35 cells
+static_assert(3 * kMaxClips - (kMaxClips - 2) + 1 <= 4 * int_cells_most(false), "INT2 grids take both sums at once");
+
 template <bool W_BF16, int EMA, int BITS, int G>
 hipError_t launch_g(const IntParams& p, hipStream_t s) {
-  if constexpr (BITS > 2) {  // INT2 grids have at most 46 cells
+  if constexpr (BITS > 2) {  // INT2 grids fit without
     if (p.cells.split) return launch_s<W_BF16, EMA, BITS, G, true>(p, s);
   }
   return launch_s<W_BF16, EMA, BITS, G, false>(p, s);
