@@ -239,7 +239,9 @@ int quasar_adamw_check(const quasar_desc* desc, const quasar_adamw* opt, const v
  * Several matrices in one launch (e.g. the seven projections of a
  * transformer layer): the same computation as one quasar_reconstruct per
  * matrix, with identical results, but a single grid, so small matrices do not
- * each pay a launch and the tail of one overlaps the others.
+ * each pay a launch and the tail of one overlaps the others (two grids for an
+ * INT clip grid that takes one kernel for the small and another for the large
+ * of the matrices, see quasar_int_path).
  *
  * desc gives everything the matrices share (format, bits, group, clips,
  * dtypes, beta2, weighting, param_dtype); its rows/cols are ignored.  Each
@@ -344,6 +346,9 @@ int64_t quasar_num_groups(const quasar_desc* desc);
  *     clips, where it is the faster one; or the environment variable
  *     QUASAR_INT_PATH=direct).  QUASAR_INT_PATH=binned selects the binned
  *     kernel for every grid whose thresholds fit its tables.
+ * For a few clip grids (INT3 g64 and symmetric INT with 9 or more clips) the
+ * binned kernel serves matrices from some rows x cols on and the direct one
+ * smaller ones.
  * Both give the same codes, chosen clip and r up to the rounding order of the
  * fp64 moment sums.
  * For RUBIN_INT3 (whose per-clip sums of Eq. rubin-fit, App. B, always come

@@ -421,18 +421,40 @@ int int_cells_per_lane(int n_cells, int group, bool split) {
 
 // Whether the binned INT kernel serves a grid of n_cells cells, and in which
 // form.  Up to 10 cells a lane it holds both sums in a cell and is the faster
-// kernel for any number of clips.  With more cells it takes one sum at a time
-// (split), and the direct kernel's time grows with the clips instead: on the
+// kernel for any number of clips (9 and 10 cells a lane leave three workgroups
+// on a compute unit where SPLIT's 12 keep four; the two were not compared
+// there).  With more cells it takes one sum at a time (split), and
+// the direct kernel's time grows with the clips instead: on the
 // Llama-3.1-8B layer set, INT3 g128 with 15 clips, split 709 us against 1172
 // direct (two passes over the weights); INT3 g64 with 10 clips 768 against
 // 987 (a pass of 12 at three wavefronts per SIMD); with 8 clips (INT4 g128,
 // one pass at four) 737 against 741, symmetric 719 against 643.
 bool int_cells_fit(int n_cells, int K, int group, bool any_fit, bool& split) {
-  if (n_cells > 128 || n_cells + 2 > quasar::kCellThr) return false;
+  if (n_cells > 128) return false;
   split = int_cells_per_lane(n_cells, group, false) > quasar::int_cells_most(false);
   if (!split) return true;
   if (!any_fit && K <= 8) return false;
   return int_cells_per_lane(n_cells, group, true) <= quasar::int_cells_most(true);
+}
+static_assert(128 + 2 <= quasar::kCellThr, "a bucket's compares read up to three thresholds");
+
+// ... and the least weights of a matrix from which SPLIT is the faster one.
+// Its groups pass through one long chain of LDS phases, which only further
+// workgroups hide (a compute unit holds four, of 4096 weights).  Direct / split,
+// us, bf16 W without a gradient, at 2^18, 2^21, 2^23 and 2^25 weights:
+//   INT3 g64, 9 clips 1.0 .. 0.5 (14 cells a lane)  9.0 / 10.1   13.6 / 14.0   40 / 34   134 / 103
+//   INT3 g64, 10 clips (16)                         8.8 / 9.9    12.4 / 13.1   38 / 35   134 / 111
+//   symmetric INT3 g64, 9 clips (14)                7.5 / 8.6    10.3 / 10.2   33 / 29   116 / 95
+//   symmetric INT3 g64, 10 clips (16)               7.4 / 9.1    10.6 / 11.5   33 / 33   121 / 115
+//   symmetric INT4 g128, 9 clips (16)               6.4 / 7.7    10.7 / 10.9   33 / 32   114 / 105
+//   symmetric INT3 g128, 15 clips (12)              9.3 / 9.3    13.8 / 12.3   38 / 30   138 / 98
+// INT3 g128 with 13 to 16 clips gains at every size (11.3 / 10.5, 16.6 / 13.4,
+// 45 / 31, 158 / 99): the direct kernel takes two passes there.
+int64_t int_split_least(int cpl, int group, bool sym) {
+  if (!sym && group == 128) return 0;
+  if (group == 128 && cpl < 16) return 1 << 19;
+  if (cpl < 16) return 5 << 19;
+  return sym ? 6 << 20 : 7 << 19;
 }
 
 // The 512-bucket table for the sorted thresholds s[0 .. m): base[b] = the
@@ -459,10 +481,11 @@ bool int_one_compare(uint8_t* base, const float* s, int m, float shift) {
 }
 
 // The binned INT kernel's tables for this clip grid (int_cells_kernel.hip):
-// every threshold T(k, b) = the least fp32 u with code_k(u) >= q0 + b.  Leaves n_cells = 0 -- the direct kernel runs --
-// when int_cells_fit says so, when a bucket needs more than three compares, or
-// when QUASAR_INT_PATH=direct is set.  QUASAR_INT_PATH=binned takes the binned
-// kernel wherever its tables fit.
+// every threshold T(k, b) = the least fp32 u with code_k(u) >= q0 + b.  Leaves
+// n_cells = 0 -- the direct kernel runs -- when int_cells_fit or int_split_least
+// says so for a matrix of `weights` weights, when a bucket needs more than
+// three compares, or when QUASAR_INT_PATH=direct is set.  QUASAR_INT_PATH=binned
+// takes the binned kernel wherever its tables fit.
 //
 // With odd qmax every clip has a threshold just below u = 0, where the fp32
 // code rounding ties at qmax/2: T(k, (qmax+1)/2) lies in (-2^-20, 0).  These
@@ -471,7 +494,7 @@ bool int_one_compare(uint8_t* base, const float* s, int m, float shift) {
 // the two (the unsafe cell) holds the u for which the cell does not fix every
 // clip's code (a few weights in ten million), and a group with saliency there
 // has its moments summed directly.
-void int_cells(quasar::IntParams& p, int K, int bits, bool sym, int group) {
+void int_cells(quasar::IntParams& p, int K, int bits, bool sym, int group, int64_t weights) {
   memset(&p.cells, 0, sizeof(p.cells));
   const char* force = getenv("QUASAR_INT_PATH");
   if (force != nullptr && strcmp(force, "direct") == 0) return;
@@ -511,6 +534,7 @@ void int_cells(quasar::IntParams& p, int K, int bits, bool sym, int group) {
   }
   if (!int_cells_fit(m + 1, K, group, any_fit, split)) return;
   const int cpl = int_cells_per_lane(m + 1, group, split);
+  if (split && !any_fit && weights < int_split_least(cpl, group, sym)) return;
   // One compare per weight when 512 buckets leave at most one threshold
   // inside each: a bucket edge is put exactly on the unsafe cell's upper end
   // (the lower end lies less than 2^-20 below it), and a threshold that is
@@ -593,7 +617,7 @@ int launch_path(const quasar_desc* d, const void* W, void* Wu, float* m, float* 
     p.r_bf16 = r_bf16;
     if (batch) p.batch = *batch;
     p.store = store;
-    int_cells(p, K, d->bits, sym, d->group);
+    int_cells(p, K, d->bits, sym, d->group, d->rows * d->cols);  // a batch: int_one_kernel
     e = quasar::launch_int(p, d->bits, d->group, w_bf16, ema_mode, st);
   } else if (is_rubin(d)) {
     quasar::RubinParams p;
@@ -666,6 +690,36 @@ int launch_path(const quasar_desc* d, const void* W, void* Wu, float* m, float* 
     e = quasar::launch_nvfp4(p, w_bf16, ema_mode, st);
   }
   return e == hipSuccess ? QUASAR_OK : QUASAR_ERR_DEVICE;
+}
+
+// Whether every matrix of a batch takes the same INT kernel as alone (only
+// grids that int_split_least decides by size can differ); if not, launches the
+// batch as two, of the matrices of either kernel, so that each gives the bytes
+// of a call of its own.  `launch` takes an array of matrices and its length.
+template <typename M, typename F>
+bool int_one_kernel(const quasar_desc* d, const M* mats, int n, F launch, int& status) {
+  if (d->format != QUASAR_INT && d->format != QUASAR_INT_SYM) return true;
+  const bool sym = d->format == QUASAR_INT_SYM;
+  const int nb = sym ? (1 << d->bits) - 2 : (1 << d->bits) - 1;
+  bool split = false;
+  // as int_cells: the most cells the grid can have
+  if (n == 1 || d->n_clips <= 8 ||
+      !int_cells_fit(d->n_clips * nb - (sym ? 0 : d->n_clips - 2) + 1, d->n_clips, d->group, true, split) || !split ||
+      int_split_least(quasar::int_cells_most(true), d->group, sym) == 0)
+    return true;
+  M part[2][QUASAR_MAX_BATCH];
+  int count[2] = {0, 0};
+  for (int i = 0; i < n; i++) {
+    quasar_desc dd = *d;
+    dd.rows = mats[i].rows;
+    dd.cols = mats[i].cols;
+    const int k = quasar_int_path(&dd);
+    part[k][count[k]++] = mats[i];
+  }
+  if (count[0] == 0 || count[1] == 0) return true;
+  status = launch(part[0], count[0]);
+  if (status == QUASAR_OK) status = launch(part[1], count[1]);
+  return false;
 }
 
 }  // namespace
@@ -762,8 +816,12 @@ int quasar_batch_check(const quasar_desc* d, const quasar_matrix* mats, int n_ma
 }
 
 int quasar_reconstruct_batch(const quasar_desc* d, const quasar_matrix* mats, int n_mats, void* stream) {
-  const int s = quasar_batch_check(d, mats, n_mats);
+  int s = quasar_batch_check(d, mats, n_mats);
   if (s != QUASAR_OK) return s;
+  if (!int_one_kernel(
+          d, mats, n_mats,
+          [&](const quasar_matrix* m, int n) { return quasar_reconstruct_batch(d, m, n, stream); }, s))
+    return s;
   quasar::BatchTable bt;
   memset(&bt, 0, sizeof(bt));
   bt.n = n_mats;
@@ -880,8 +938,15 @@ int quasar_adamw_batch_check(const quasar_desc* d, const quasar_adamw* opt, cons
 
 int quasar_adamw_reconstruct_batch(const quasar_desc* d, const quasar_adamw* opt,
                                    const quasar_adamw_matrix* mats, int n_mats, int r_dtype, void* stream) {
-  const int s = quasar_adamw_batch_check(d, opt, mats, n_mats, r_dtype);
+  int s = quasar_adamw_batch_check(d, opt, mats, n_mats, r_dtype);
   if (s != QUASAR_OK) return s;
+  if (!int_one_kernel(
+          d, mats, n_mats,
+          [&](const quasar_adamw_matrix* m, int n) {
+            return quasar_adamw_reconstruct_batch(d, opt, m, n, r_dtype, stream);
+          },
+          s))
+    return s;
   const quasar_adamw_matrix& x0 = mats[0];
   // the shared fields come from the descriptor; slot 0 also fills the
   // single-matrix fields (the by-products are the slots')
@@ -951,6 +1016,6 @@ extern "C" int quasar_int_path(const quasar_desc* d) {
   quasar::IntParams p;
   memset(&p, 0, sizeof(p));
   int_clip_tables(d, p);
-  int_cells(p, d->n_clips, d->bits, d->format == QUASAR_INT_SYM, d->group);
+  int_cells(p, d->n_clips, d->bits, d->format == QUASAR_INT_SYM, d->group, d->rows * d->cols);
   return p.cells.n_cells > 0 ? 1 : 0;
 }

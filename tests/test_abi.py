@@ -392,6 +392,20 @@ def test_int_path_choice():
     assert Q.quasar_int_path(_int_desc(clips=(1.0, 1.5))) == Q.ERR_ARG
 
 
+@pytest.mark.parametrize("fmt,bits,group,k,least", [
+    ("int", 3, 64, 9, 5 << 19), ("int", 3, 64, 10, 7 << 19), ("int_sym", 3, 64, 9, 5 << 19),
+    ("int_sym", 3, 64, 10, 6 << 20), ("int_sym", 4, 128, 9, 6 << 20), ("int_sym", 3, 128, 14, 1 << 19),
+    ("int_sym", 3, 128, 16, 1 << 19), ("int", 3, 128, 13, 0), ("int", 3, 128, 16, 0), ("int", 2, 64, 16, 0)])
+def test_int_path_by_size(fmt, bits, group, k, least):
+    """Grids for which the binned kernel is the faster one from some size on."""
+    kw = dict(fmt=fmt, bits=bits, group=group, clips=tuple(np.linspace(1.0, 0.5, k)), cols=1024)
+    rows = least // 1024
+    assert Q.quasar_int_path(_int_desc(rows=max(rows, 1), **kw)) == 1
+    if rows:
+        assert Q.quasar_int_path(_int_desc(rows=rows - 1, **kw)) == 0
+        assert _with_path("binned", lambda: Q.quasar_int_path(_int_desc(rows=1, **kw))) == 1
+
+
 class _ArrayLike:
     def __array__(self, dtype=None, copy=None):
         return np.array([1.0, 0.8], dtype=dtype or np.float64)

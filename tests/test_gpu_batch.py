@@ -172,6 +172,19 @@ def test_batch_nvfp4_amax_from_batched_pass():
         _same(f"nvfp4.auto.{i}", a, b)
 
 
+@pytest.mark.parametrize("fmt,bits,group,k", [("int", 3, 64, 9), ("int_sym", 4, 128, 9)])
+@pytest.mark.parametrize("shapes", [[(1537, 4096), (64, 256), (17, 384), (1540, 4096)],  # both INT kernels
+                                    [(600, 4096)] * 8])                                  # small ones only
+def test_batch_of_sizes_that_take_different_kernels(fmt, bits, group, k, shapes):
+    """Each matrix of a batch takes the kernel that it takes alone, whatever
+    the others' sizes: every byte is a single call's."""
+    clips = tuple(float(x) for x in synth.clip_grid(1.0, 0.5, k))
+    paths = {Q.quasar_int_path(Q.Descriptor(r, c, fmt=fmt, bits=bits, group=group, clips=clips)) for r, c in shapes}
+    assert paths == ({0, 1} if len(set(shapes)) > 1 else {0})
+    _check_batch(f"batch.sizes.{fmt}{bits}", _draw(shapes, 21, w_bf16=True, ema=True), fmt=fmt, bits=bits,
+                 group=group, clips=clips, oracle_check=False)
+
+
 def test_adamw_batch_of_one_takes_the_matrix_shape():
     """The descriptor's rows and cols are ignored, with one matrix as with more."""
     clips = tuple(float(x) for x in synth.clip_grid(1.0, 0.6, 8))
@@ -189,3 +202,22 @@ def test_adamw_batch_of_one_takes_the_matrix_shape():
     _same("adamw.one", want, o, keys=("codes", "scales", "zeros", "r", "best_clip", "err"))
     for a, b in zip(one[:3], (W, m, v)):
         assert torch.equal(a.view(torch.int32), b.view(torch.int32))
+
+
+def test_adamw_batch_of_sizes_that_take_different_kernels():
+    clips = tuple(float(x) for x in synth.clip_grid(1.0, 0.5, 10))
+    shapes = [(64, 256), (1537, 4096), (17, 384)]
+    kw = dict(lr=1e-3, step=2, fmt="int", bits=3, group=64, clips=clips)
+    mats = []
+    for i, (r, c) in enumerate(shapes):
+        W, v, g = synth.gen_matrix(r, c, 31 + i, w_bf16=False, ema=True, device="cuda")
+        m, v = synth.gen_adamw_state(r, c, 31 + i, v, device="cuda")
+        mats.append((W, m, v.contiguous(), g))
+    copies = [[t.clone() for t in x] for x in mats]
+    outs = Q.adamw_reconstruct_batch(copies, **kw)
+    for i, (x, y, o) in enumerate(zip(mats, copies, outs)):
+        one = Q.adamw_reconstruct(*x, **kw)
+        torch.cuda.synchronize()
+        _same(f"adamw.sizes.{i}", one, o)
+        for a, b in zip(x[:3], y[:3]):
+            assert torch.equal(a.view(torch.int32), b.view(torch.int32))
