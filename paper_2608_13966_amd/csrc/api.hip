@@ -782,7 +782,8 @@ int quasar_reconstruct_noalloc(const quasar_desc* d, const void* W, float* v, co
     if (ws == nullptr) return QUASAR_ERR_DEVICE;
   }
   // the same validation and launches as quasar_reconstruct, with the static
-  // array as its workspace (the absmax pass clears it with a kernel first)
+  // array as its workspace (the absmax pass stores its maxima there, or, for a
+  // matrix beyond kAbsPartialChunks, clears one with a kernel first)
   const int s = quasar_check(d, W, v, g, codes, scales, zeros, r, best_clip, err, tensor_scale, tensor_amax, ws,
                              need);
   if (s != QUASAR_OK) return s;

@@ -178,11 +178,6 @@ struct WRegs<true> {
 #pragma unroll
     for (int k = 0; k < 8; k++) d[k] = pack_bf16x2(w[2 * k], w[2 * k + 1]);
   }
-  __device__ __forceinline__ void store(void* base, int64_t e0) const {
-    uint16_t* p = reinterpret_cast<uint16_t*>(base) + e0;
-    st128(p, make_uint4(d[0], d[1], d[2], d[3]));
-    st128(p + 8, make_uint4(d[4], d[5], d[6], d[7]));
-  }
 };
 template <>
 struct WRegs<false> {
@@ -193,7 +188,6 @@ struct WRegs<false> {
 #pragma unroll
     for (int i = 0; i < 16; i++) f[i] = w[i];
   }
-  __device__ __forceinline__ void store(void* base, int64_t e0) const { store16<false>(base, e0, f); }
 };
 
 // Constants of one AdamW step, computed on the host.
@@ -261,9 +255,6 @@ __device__ __forceinline__ float max_f32(float a, float b) {
   return r;
 }
 
-// All-reduce over aligned runs of L consecutive lanes (L in 1, 2, 4, 8, 16).
-// The patterns pair lanes symmetrically, and IEEE addition / min / max are
-// commutative, so every lane of a run ends with a bit-identical result.
 // x combined with the x of the lane a DPP control names, in one instruction
 // (a separate DPP move feeding the inline min or max would be two).  A DPP
 // operand may not be read within two wait states of its VALU write, which the
@@ -285,6 +276,9 @@ QUASAR_DPP_MINMAX(half_mirror, "row_half_mirror")
 QUASAR_DPP_MINMAX(mirror, "row_mirror")
 #undef QUASAR_DPP_MINMAX
 
+// All-reduce over aligned runs of L consecutive lanes (L in 1, 2, 4, 8, 16).
+// The patterns pair lanes symmetrically, and IEEE addition / min / max are
+// commutative, so every lane of a run ends with a bit-identical result.
 template <int L>
 __device__ __forceinline__ float run_min(float x) {
   if constexpr (L >= 2) x = xor1_min(x);

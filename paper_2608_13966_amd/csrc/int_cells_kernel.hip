@@ -33,8 +33,9 @@
 // them exactly as the direct form does (int_common.h).
 //
 // What bounds it: on the Llama-3.1-8B layer set (INT2 g64, 12 clips, EMA, 14.4
-// bytes per weight) a launch moves 4.9 TB/s, about a plain copy's rate, with
-// the VALU and the LDS each busy two thirds of the time.  Measured steps, all
+// bytes per weight) a launch moves 5.0 TB/s, about a plain copy's rate, with
+// the VALU busy 72% and the LDS 60% of the time (SQ_ACTIVE_INST_VALU and
+// SQ_LDS_IDX_ACTIVE over the compute units' cycles).  Measured steps, all
 // on that set: fp64 suffix sums, rounded cell by cell in two passes over the
 // LDS, and binning and atomics as two loops: 688 us; in integers, one pass in
 // registers, one loop, one compare per weight: 643; the fit's tests once per
@@ -42,10 +43,14 @@
 // stores non-temporal: 624 (Qwen3-0.6B set, INT3 with 8 clips: 48.9, 42.0, 41.8,
 // 41.2, 39.9).
 // Forms.  Both sums in a cell (16 bytes) keep four workgroups on a compute
-// unit up to 10 cells a lane.  Beyond that the cells' LDS would leave two: the
-// SPLIT form takes h and then h w through 8-byte cells (each weight's cell is
-// kept, one byte).  INT3 g128 with 15 clips (93 cells), the Llama set: 709 us;
-// both sums at once 1018; the direct kernel 1172.  A form with 8 weights per
+// unit up to 8 cells a lane and three at 9 and 10 (46.5 KB of LDS).  At 12 and
+// more they would leave two: the SPLIT form takes h and then h w through
+// 8-byte cells (each weight's cell is kept, one byte), and keeps four.  INT3
+// g128 with 15 clips (93 cells), the Llama set: 709 us; both sums at once 1018;
+// the direct kernel 1172.  At g64 SPLIT meets the 128 VGPRs of four wavefronts
+// and spills 1 with the EMA on fp32 W, 2 to 10 with the AdamW step; from
+// int_split_least's sizes on it is still 2 to 19% faster than the direct kernel there
+// (INT3, 9 and 10 clips, fp32 W, AdamW).  A form with 8 weights per
 // lane (half the groups per wavefront, so half the LDS) took 750 us there,
 // and 59 against 45 us on the Qwen3-0.6B set (INT3, 8 clips): its per-group
 // work is spread over twice the wavefronts.

@@ -382,12 +382,12 @@ __device__ __forceinline__ float chunk_absmax(uint4 t) {
   return m;
 }
 
+constexpr int64_t kAbsChunks = (int64_t)kThreads * kAbsSpan;
+
 // One workgroup per span of kAbsChunks 16-byte chunks of one matrix: lane t
 // loads chunks t, t + 256, ... (each load instruction reads 1 KB contiguous per
 // wavefront), kAbsBatch loads in flight at a time; then a DPP / LDS maximum
 // and at most one atomicMax on the fp32 bit pattern per workgroup.
-constexpr int64_t kAbsChunks = (int64_t)kThreads * kAbsSpan;
-
 //
 // NT: non-temporal loads, for matrices larger than the last-level cache: what
 // this pass would leave there is gone when the reconstruction reads W (Llama

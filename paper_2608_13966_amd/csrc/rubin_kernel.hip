@@ -50,9 +50,9 @@
 // codebook entry b of clip k.
 //
 // What bounds it: on the Llama-3.1-8B layer set (15 clips, EMA, 14.4 bytes per
-// weight) 711 us, 4.4 TB/s, with the LDS busy three quarters of the time (24
-// atomics per wavefront at random cells, 16 cycles each: 400 of its 800
-// cycles) and the VALU about as much.  754 us before the limbs were split with
+// weight) 711 us, 4.4 TB/s, with the LDS busy 78% of the time (24 atomics per
+// wavefront at random cells, 16 cycles each: about 400 of its 750 cycles) and
+// the VALU 77%.  754 us before the limbs were split with
 // three fmas (six instructions before), the argmin taken once over all clips,
 // the tie and lost-saliency tests made by one unsigned minimum each, and the
 // codes emitted as bytes that permute the codebook (no LDS lookup per weight),
