@@ -51,26 +51,28 @@ def source_fingerprint() -> str:
 def binned_valu_ops_per_weight(wl, n_cells: int) -> float:
     """VALU lane-operations per weight of the binned INT kernel (the clips'
     moments from per-group threshold-cell sums): per weight, the range (2),
-    the position u (1), its bucket (4) and cell (one compare and add: 2),
-    the packed cell (1), h and h w as exact integers (conversions, product,
-    sum h w^2, two scaled roundings with their high-word corrections, cell
-    address: 10), the emitted code, r and pack (5), and the EMA (3); per
-    group of G weights, the suffix scan (about 12 per cell), each clip's
-    moments from its NB suffix sums and its ratio test (3 NB + 11 per clip)
-    and one fit and score per 16 weights (about 45)."""
+    the position u (1), its bucket (4) and cell (one compare and a bit field:
+    2), h and h w as exact integers (conversions, product, sum h w^2, two
+    scaled roundings with their high-word corrections, cell address: 10), the
+    emitted code, r and pack (5), and the EMA (3); per group of G weights, the
+    suffix sums of two 64-bit integers over the cells (about 6 per cell), each
+    clip's moments from its NB steps (three 64-bit additions each) and its
+    ratio test (6 NB + 11 per clip) and one fit and score per 16 weights
+    (about 45)."""
     K = len(wl.clips)
     qmax = (1 << (wl.bits - 1)) - 1 if wl.fmt == "int_sym" else (1 << wl.bits) - 1
     nb = 2 * qmax if wl.fmt == "int_sym" else qmax
     pre = 10.0 if wl.adamw else (3.0 if wl.ema else 0.0)
-    per_group = 12.0 * n_cells + (3.0 * nb + 11.0) * K + 45.0 * (wl.group / 16)
-    return 25.0 + pre + per_group / wl.group
+    per_group = 6.0 * n_cells + (6.0 * nb + 11.0) * K + 45.0 * (wl.group / 16)
+    return 24.0 + pre + per_group / wl.group
 
 
 def int_kernel_choice(wl):
     """(kernel name, cells) of the INT kernel the library takes for this
-    workload's clip grid (quasar_int_path; host-only)."""
+    workload's clip grid and its largest matrix (quasar_int_path; host-only)."""
     from paper_2608_13966_amd import quasar as Q
-    d = Q.Descriptor(8, wl.group, fmt=wl.fmt, bits=wl.bits, group=wl.group, clips=wl.clips,
+    rows, cols = max(((r, c) for _, r, c in wl.shapes), key=lambda rc: rc[0] * rc[1])
+    d = Q.Descriptor(rows, cols, fmt=wl.fmt, bits=wl.bits, group=wl.group, clips=wl.clips,
                      w_dtype=Q.BF16 if wl.w_bf16 else Q.F32)
     if Q.quasar_int_path(d) == 1:
         return "int_cells_kernel", int_cells_count(wl)
