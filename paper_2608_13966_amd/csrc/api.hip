@@ -427,8 +427,11 @@ int int_cells_per_lane(int n_cells, int group, bool split) {
 // the direct kernel's time grows with the clips instead: on the
 // Llama-3.1-8B layer set, INT3 g128 with 15 clips, split 709 us against 1172
 // direct (two passes over the weights); INT3 g64 with 10 clips 768 against
-// 987 (a pass of 12 at three wavefronts per SIMD); with 8 clips (INT4 g128,
-// one pass at four) 737 against 741, symmetric 719 against 643.
+// 987 (a pass of 12 at three wavefronts per SIMD).  With up to 8 clips, one
+// direct pass at four or five wavefronts, it loses: on one matrix of 2^18 to
+// 2^26 weights INT4 g128 takes 1.37 to 1.07 times as long split, symmetric 1.48
+// to 1.06, symmetric INT3 g64 1.31 to 1.01 (INT3 g64 with 7 and 8 clips 1.22 at
+// 2^18, even at 2^22, 0.91 to 0.97 from 2^24 on).
 bool int_cells_fit(int n_cells, int K, int group, bool any_fit, bool& split) {
   if (n_cells > 128) return false;
   split = int_cells_per_lane(n_cells, group, false) > quasar::int_cells_most(false);
@@ -448,7 +451,7 @@ static_assert(128 + 2 <= quasar::kCellThr, "a bucket's compares read up to three
 //   symmetric INT3 g64, 10 clips (16)               7.4 / 9.1    10.6 / 11.5   33 / 33   121 / 115
 //   symmetric INT4 g128, 9 clips (16)               6.4 / 7.7    10.7 / 10.9   33 / 32   114 / 105
 //   symmetric INT3 g128, 15 clips (12)              9.3 / 9.3    13.8 / 12.3   38 / 30   138 / 98
-// INT3 g128 with 13 to 16 clips gains at every size (11.3 / 10.5, 16.6 / 13.4,
+// INT3 g128 with 13 to 16 clips (12, 14) gains at every size (11.3 / 10.5, 16.6 / 13.4,
 // 45 / 31, 158 / 99): the direct kernel takes two passes there.
 int64_t int_split_least(int cpl, int group, bool sym) {
   if (!sym && group == 128) return 0;

@@ -46,7 +46,7 @@
 // unit up to 8 cells a lane and three at 9 and 10 (46.5 KB of LDS).  At 12 and
 // more they would leave two: the SPLIT form takes h and then h w through
 // 8-byte cells (each weight's cell is kept, one byte), and keeps four.  INT3
-// g128 with 15 clips (93 cells), the Llama set: 709 us; both sums at once 1018;
+// g128 with 15 clips (91 cells), the Llama set: 709 us; both sums at once 1018;
 // the direct kernel 1172.  At g64 SPLIT meets the 128 VGPRs of four wavefronts
 // and spills 1 with the EMA on fp32 W, 2 to 10 with the AdamW step; from
 // int_split_least's sizes on it is still 2 to 19% faster than the direct kernel there

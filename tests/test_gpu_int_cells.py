@@ -15,15 +15,18 @@ pytestmark = pytest.mark.gpu
 # (fmt, bits, group, clips): the cells a group has, and what is at its edge
 GRIDS = [
     ("int", 2, 64, (1.0,)),                                # 4 cells, the fewest
-    ("int_sym", 2, 128, tuple(synth.clip_grid(1.0, 0.9, 16))),  # no tie cells; dense: several compares
+    ("int_sym", 2, 128, tuple(synth.clip_grid(1.0, 0.9, 16))),  # no tie cells; dense: three compares
     ("int", 2, 64, tuple(synth.clip_grid(1.0, 0.3, 16))),  # 35 cells, 10 a lane
-    ("int", 3, 64, tuple(synth.clip_grid(1.0, 0.65, 8))),  # 52 cells: one sum at a time, 14 a lane
-    ("int", 3, 64, tuple(synth.clip_grid(1.0, 0.5, 9))),   # 58 cells, 16 a lane: the most for g64
-    ("int", 3, 128, tuple(synth.clip_grid(1.0, 0.6, 11))),  # 70 cells: the last with both sums at once
-    ("int", 3, 128, tuple(synth.clip_grid(1.0, 0.6, 13))),  # 82 cells: the first with one, 12 a lane
-    ("int", 3, 128, tuple(synth.PAPER_CLIPS)),             # exact-arithmetic ties between clips: two compares
+    ("int", 3, 64, tuple(synth.clip_grid(1.0, 0.65, 8))),  # 51 cells: one sum at a time, 14 a lane
+    ("int", 3, 64, tuple(synth.clip_grid(1.0, 0.5, 9))),   # 56 cells: the last with 14 a lane; two compares
+    ("int", 3, 64, tuple(synth.clip_grid(1.0, 0.6, 10))),  # 63 cells, 16 a lane: the most for g64
+    ("int", 3, 128, tuple(synth.clip_grid(1.0, 0.6, 11))),  # 68 cells
+    ("int", 3, 128, tuple(synth.clip_grid(1.0, 0.5, 13))),  # 80 cells: the last with both sums at once
+    ("int", 3, 128, tuple(synth.clip_grid(1.0, 0.65, 13))),  # 81 cells: the first with one, 12 a lane
+    ("int", 3, 128, tuple(synth.clip_grid(1.0, 0.6, 13))),  # 79 cells
+    ("int", 3, 128, tuple(synth.PAPER_CLIPS)),             # 91 cells; ties between clips in exact arithmetic: three compares
     ("int", 3, 128, (1.0, 1.0, 0.5, 0.5, 0.25, 0.25, 0.75, 0.75, 0.375)),  # equal and doubled factors
-    ("int", 3, 128, tuple(synth.clip_grid(1.0, 0.3, 16))),  # 100 cells
+    ("int", 3, 128, tuple(synth.clip_grid(1.0, 0.3, 16))),  # 99 cells, 14 a lane
     ("int", 4, 128, tuple(synth.clip_grid(1.0, 0.65, 8))),  # 114 cells, 16 a lane, 15 steps
     ("int_sym", 4, 128, tuple(synth.clip_grid(1.0, 0.65, 9))),  # 127 cells, the most for g128, 14 steps
 ]
